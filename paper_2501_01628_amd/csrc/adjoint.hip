@@ -40,7 +40,7 @@ constexpr float kLn2 = 0.6931471805599453f;
 // One workgroup's work: tiles first_tile .. first_tile + kWaves - 1 of the
 // partial (p, bp), one per wavefront.
 template <typename TS, int kWaves>
-__device__ inline void backward_tiles(const MarchParams& p, const BackwardParams& bp, int first_tile) {
+__device__ __forceinline__ void backward_tiles(const MarchParams& p, const BackwardParams& bp, int first_tile) {
     __shared__ TFTable tft;
     __shared__ float gtf[256 * 4];
     __shared__ float tbuf_all[kWaves][kMaxCkptInterval * 64];
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kWaves * 64) void march_backward_many(const Backwar
         if (block_start[mid] <= b) lo = mid; else hi = mid - 1;
     }
     lo = __builtin_amdgcn_readfirstlane(lo);      // uniform: the job's fields load as scalars
-    const BackwardJob& J = jobs[lo];
+    const BackwardJob& J = const_entry(jobs, lo);
     backward_tiles<TS, kWaves>(J.p, J.bp, (b - __builtin_amdgcn_readfirstlane(block_start[lo])) * kWaves);
 }
 

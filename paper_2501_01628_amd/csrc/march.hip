@@ -297,7 +297,7 @@ __device__ inline void finish(const MarchParams& p, bool valid, long long pix, f
 // One 8x8 tile of partial p per 64-thread workgroup, every lane marching
 // from HBM.
 template <typename TS, bool kCkpt>
-__device__ inline void march_tile_hbm(const MarchParams& p, int tile) {
+__device__ __forceinline__ void march_tile_hbm(const MarchParams& p, int tile) {
     __shared__ TFTable tft;
     const int lane = threadIdx.x;
     load_tf(tft, p.tf, p.dt, lane, 64);
@@ -338,8 +338,8 @@ __global__ __launch_bounds__(64) void march_checkpointed_many(const MarchParams*
         const int mid = (lo + hi + 1) >> 1;
         if (tile_start[mid] <= b) lo = mid; else hi = mid - 1;
     }
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    march_tile_hbm<TS, true>(jobs[lo], b - __builtin_amdgcn_readfirstlane(tile_start[lo]));
+    lo = uniform_i(lo);
+    march_tile_hbm<TS, true>(const_entry(jobs, lo), b - __builtin_amdgcn_readfirstlane(tile_start[lo]));
 }
 
 // ------------------------------------------------- shared by the staged kernels
@@ -372,8 +372,6 @@ __device__ inline void wg_reduce(float (&v)[N], const bool (&is_max)[N], float (
         v[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
     }
 }
-
-__device__ inline int uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // ------------------------------------------------------- staged kernel (slabs)
 // A 256-thread workgroup owns a 16x16 pixel tile (one wavefront per 8x8
@@ -1480,16 +1478,18 @@ __device__ inline void queue_loop(const QueueParams& q, Shared& sh, TFTable& tft
             // after at most one ticket past its end
             if (tid == 0) ticket = lo_t + atomicAdd(q.head + part, 1);
             __syncthreads();
-            const int t = ticket;
+            const int t = uniform_i(ticket);
             __syncthreads();
             if (t >= hi_t) break;
-            // job of ticket t: the last j with tile_start[j] <= t
+            // job of ticket t: the last j with tile_start[j] <= t (uniform, so
+            // that the job's fields are scalar loads into scalar registers)
             int lo = 0, hi = q.n_jobs - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
                 if (q.tile_start[mid] <= t) lo = mid; else hi = mid - 1;
             }
-            const MarchParams& p = q.jobs[lo];
+            lo = uniform_i(lo);
+            const MarchParams& p = const_entry(q.jobs, lo);
             if (p.tf.rgba != tf_loaded || p.tf.opacity_scale != scale_loaded || p.dt != dt_loaded) {
                 load_tf(tft, p.tf, p.dt, tid, blockDim.x);
                 tf_loaded = p.tf.rgba;
@@ -1497,7 +1497,7 @@ __device__ inline void queue_loop(const QueueParams& q, Shared& sh, TFTable& tft
                 dt_loaded = p.dt;
                 if (sync_tf) __syncthreads();
             }
-            tile_fn(p, t - q.tile_start[lo]);
+            tile_fn(p, t - uniform_i(q.tile_start[lo]));
             __syncthreads();
         }
     }

@@ -16,6 +16,19 @@ namespace dpvr {
 constexpr int kSlab = 16;         // anchor block = slab of kSlab slices along the ray's w axis
 constexpr float kLog2e = 1.4426950408889634f;
 
+__device__ inline int uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Entry i (wavefront-uniform) of a table that nothing writes while the kernel
+// runs, read through the constant address space: scalar loads into scalar
+// registers.  Through a plain global pointer every field is a vector load
+// into VGPRs, repeated after each barrier (the 32-wide ring march held 168
+// VGPRs and 120 scratch accesses that way, 128 and 14 this way).
+template <typename T>
+__device__ inline const T& const_entry(const T* table, int i) {
+    typedef __attribute__((address_space(4))) const T entry_t;
+    return *(const T*)((entry_t*)table + i);
+}
+
 struct RaySetup {
     double o[3], d[3];
     long long kf, kl;             // first / last owned sample index
