@@ -1721,8 +1721,8 @@ struct vr_tetpart_s {
     int32_t n_input_vertices = 0;        // vertices whose values the caller gives
     std::vector<int32_t> centre_nodes;   // cell centres: 8 node indices each (-1 padded)
     // device workspace: [planes][vals][owned][tets][cell_start][cell_tets][nbr][centre_nodes]
-    // [bvh_nodes][bvh_tets], each 256-aligned
-    size_t off[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    // [bvh_nodes][bvh_tets][cell_head][planes32][affine], each 256-aligned
+    size_t off[13] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     size_t need = 0;
     char* ws = nullptr;
     bool has_values = false;
@@ -1730,7 +1730,7 @@ struct vr_tetpart_s {
 
 namespace {
 
-size_t tetpart_layout(const TetTables& t, const std::vector<int32_t>& centre_nodes, size_t off[10]) {
+size_t tetpart_layout(const TetTables& t, const std::vector<int32_t>& centre_nodes, size_t off[13]) {
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t nt = (size_t)t.n_tets;
     size_t o = 0;
@@ -1744,7 +1744,37 @@ size_t tetpart_layout(const TetTables& t, const std::vector<int32_t>& centre_nod
     off[7] = o; o += up(centre_nodes.size() * sizeof(int32_t));
     off[8] = o; o += up(t.bvh_nodes.size() * sizeof(int32_t));
     off[9] = o; o += up(t.bvh_tets.size() * sizeof(int32_t));
+    off[10] = o; o += up(t.cell_head.size() * sizeof(int32_t));
+    off[11] = o; o += up(t.planes32.size() * sizeof(float));
+    off[12] = o; o += up(nt * 4 * sizeof(double));
     return o;
+}
+
+// The part's tables in its workspace, as the kernels see them.
+TetPartK tetpart_tables(vr_tetpart q) {
+    const TetTables& t = q->tab;
+    TetPartK k{};
+    k.planes = reinterpret_cast<const double*>(q->ws + q->off[0]);
+    k.planes32 = reinterpret_cast<const float*>(q->ws + q->off[11]);
+    k.affine = reinterpret_cast<const double*>(q->ws + q->off[12]);
+    k.err32 = t.err32;
+    k.vals = reinterpret_cast<const float*>(q->ws + q->off[1]);
+    k.owned = reinterpret_cast<const uint32_t*>(q->ws + q->off[2]);
+    k.cell_start = reinterpret_cast<const int32_t*>(q->ws + q->off[4]);
+    k.cell_tets = reinterpret_cast<const int32_t*>(q->ws + q->off[5]);
+    k.nbr = reinterpret_cast<const int32_t*>(q->ws + q->off[6]);
+    k.cell_head = reinterpret_cast<const int32_t*>(q->ws + q->off[10]);
+    k.bvh_nodes = reinterpret_cast<const int32_t*>(q->ws + q->off[8]);
+    k.bvh_tets = reinterpret_cast<const int32_t*>(q->ws + q->off[9]);
+    for (int c = 0; c < 3; ++c) {
+        k.lo[c] = t.lo[c];
+        k.hi[c] = t.hi[c];
+        k.glo[c] = t.glo[c];
+        k.ginv[c] = t.ginv[c];
+        k.gdim[c] = t.gdim[c];
+    }
+    k.n_tets = t.n_tets;
+    return k;
 }
 
 // Frame workspace of n parts: [TetPartK x n][tile prefix n + 1], then per
@@ -1762,24 +1792,7 @@ size_t tetframe_layout(vr_context ctx, int32_t n, const vr_tetpart* parts, int32
         if (t.n_tets > 0) roi_for_box(ctx->cam, t.lo, t.hi, roi);
         const size_t np = (size_t)roi[2] * roi[3];
         if (jobs) {
-            TetPartK k{};
-            const vr_tetpart q = parts[i];
-            k.planes = reinterpret_cast<const double*>(q->ws + q->off[0]);
-            k.vals = reinterpret_cast<const float*>(q->ws + q->off[1]);
-            k.owned = reinterpret_cast<const uint32_t*>(q->ws + q->off[2]);
-            k.cell_start = reinterpret_cast<const int32_t*>(q->ws + q->off[4]);
-            k.cell_tets = reinterpret_cast<const int32_t*>(q->ws + q->off[5]);
-            k.nbr = reinterpret_cast<const int32_t*>(q->ws + q->off[6]);
-            k.bvh_nodes = reinterpret_cast<const int32_t*>(q->ws + q->off[8]);
-            k.bvh_tets = reinterpret_cast<const int32_t*>(q->ws + q->off[9]);
-            for (int c = 0; c < 3; ++c) {
-                k.lo[c] = t.lo[c];
-                k.hi[c] = t.hi[c];
-                k.glo[c] = t.glo[c];
-                k.ginv[c] = t.ginv[c];
-                k.gdim[c] = t.gdim[c];
-            }
-            k.n_tets = t.n_tets;
+            TetPartK k = tetpart_tables(parts[i]);
             k.roi_x0 = roi[0];
             k.roi_y0 = roi[1];
             k.roi_w = roi[2];
@@ -1952,7 +1965,7 @@ vr_status vr_tetpart_attach(vr_tetpart q, void* workspace, size_t workspace_byte
         size_t off;
         const void* src;
         size_t bytes;
-    } copies[9] = {{q->off[0], t.planes.data(), t.planes.size() * sizeof(double)},
+    } copies[11] = {{q->off[0], t.planes.data(), t.planes.size() * sizeof(double)},
                    {q->off[2], t.owned.data(), t.owned.size() * sizeof(uint32_t)},
                    {q->off[3], t.tets.data(), t.tets.size() * sizeof(int32_t)},
                    {q->off[4], t.cell_start.data(), t.cell_start.size() * sizeof(int32_t)},
@@ -1960,7 +1973,9 @@ vr_status vr_tetpart_attach(vr_tetpart q, void* workspace, size_t workspace_byte
                    {q->off[6], t.nbr.data(), t.nbr.size() * sizeof(int32_t)},
                    {q->off[7], q->centre_nodes.data(), q->centre_nodes.size() * sizeof(int32_t)},
                    {q->off[8], t.bvh_nodes.data(), t.bvh_nodes.size() * sizeof(int32_t)},
-                   {q->off[9], t.bvh_tets.data(), t.bvh_tets.size() * sizeof(int32_t)}};
+                   {q->off[9], t.bvh_tets.data(), t.bvh_tets.size() * sizeof(int32_t)},
+                   {q->off[10], t.cell_head.data(), t.cell_head.size() * sizeof(int32_t)},
+                   {q->off[11], t.planes32.data(), t.planes32.size() * sizeof(float)}};
     hipError_t e = hipSuccess;
     for (const auto& c : copies)
         if (e == hipSuccess && c.bytes > 0)
@@ -1982,6 +1997,13 @@ vr_status vr_tetpart_set_values(vr_tetpart q, const float* values) {
     hipError_t e = launch_tet_values(values, q->n_input_vertices, reinterpret_cast<const int32_t*>(q->ws + q->off[7]),
                                      reinterpret_cast<const int32_t*>(q->ws + q->off[3]), q->tab.n_tets,
                                      reinterpret_cast<float*>(q->ws + q->off[1]), ctx->stream);
+    if (e == hipSuccess) {
+        const int32_t no_tiles = 0;
+        TetFrameParams f{};
+        f.tile_start = &no_tiles;
+        f.one = tetpart_tables(q);
+        e = launch_tet_frame(f, kTetAffine, ctx->stream);
+    }
     if (e != hipSuccess) return fail(ctx, VR_ERR_DEVICE, "%s: %s", who, hipGetErrorString(e));
     q->has_values = true;
     return ok(ctx);

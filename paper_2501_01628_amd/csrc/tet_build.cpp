@@ -137,6 +137,94 @@ void build_bvh(const double* V, const int32_t* T, int32_t nt, TetTables& out) {
 
 }  // namespace
 
+// The cells' heads.  Distances to the nearest non-empty cell, one axis after
+// another: along x from the lists, then along y and z the minimum over the
+// neighbours within kFarMax - 1 cells of the larger of their distance so far
+// and the step to them.
+static void build_cell_heads(TetTables& out) {
+    const size_t gx = (size_t)out.gdim[0], gy = (size_t)out.gdim[1], gz = (size_t)out.gdim[2];
+    const size_t cells = gx * gy * gz;
+    std::vector<uint8_t> a(cells), b(cells);
+    for (size_t row = 0; row < cells; row += gx) {
+        int d = kFarMax;
+        for (size_t x = 0; x < gx; ++x) {
+            d = out.cell_start[row + x + 1] > out.cell_start[row + x] ? 0 : std::min(d + 1, kFarMax);
+            a[row + x] = (uint8_t)d;
+        }
+        d = kFarMax;
+        for (size_t x = gx; x-- > 0;) {
+            d = std::min<int>(a[row + x], std::min(d + 1, kFarMax));
+            a[row + x] = (uint8_t)d;
+        }
+    }
+    // whole runs of `len` consecutive cells move by `stride` at once
+    auto pass = [](const std::vector<uint8_t>& src, std::vector<uint8_t>& dst, size_t n, size_t stride,
+                   size_t blocks) {
+        dst = src;
+        for (size_t blk = 0; blk < blocks; ++blk)
+            for (size_t i = 1; i < std::min<size_t>(kFarMax, n); ++i) {
+                uint8_t* D = dst.data() + blk * n * stride;
+                const uint8_t* S = src.data() + blk * n * stride;
+                const size_t len = (n - i) * stride, off = i * stride;
+                const uint8_t step = (uint8_t)i;
+                for (size_t c = 0; c < len; ++c) {
+                    D[c] = std::min(D[c], std::max(step, S[c + off]));
+                    D[c + off] = std::min(D[c + off], std::max(step, S[c]));
+                }
+            }
+    };
+    pass(a, b, gy, gx, gz);
+    pass(b, a, gz, gx * gy, 1);
+    out.cell_head.assign(4 * (cells + 1), 0);
+    for (size_t c = 0; c < cells; ++c) {
+        const int32_t first = out.cell_start[c], n = out.cell_start[c + 1] - first;
+        int32_t* h = &out.cell_head[4 * c];
+        if (n == 0) {
+            h[0] = -(int32_t)a[c];
+            continue;
+        }
+        h[0] = out.cell_tets[(size_t)first];
+        h[1] = n > 1 ? out.cell_tets[(size_t)first + 1] : -1;
+        h[2] = first + std::min(n, 2);
+        h[3] = first + n;
+    }
+    out.cell_head[4 * cells] = -1;
+}
+
+// The float32 barycentric planes.  With |x| <= X per axis (X: twice the
+// grid's largest extent, which holds the samples two steps beyond the box),
+// u = 2^-24, M = the sum of the three |m|_1 and |c_i| <= |m_i|_1 X (the plane
+// meets the box): rounding m, c and x costs 3 u |m_i|_1 X and the fused steps
+// 6 u |m_i|_1 X per coordinate, so 9 u M X for their sum and 6 u M X + 3 u for
+// the subtractions from one (M X >= 1); the float64 evaluation on both sides
+// 2^-49 M (X + |glo|).  16 u M X with the doubled extent bounds it twice over.
+static void build_planes32(TetTables& out) {
+    double X = 0.0, G = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        X = std::fmax(X, 2.0 * (double)out.gdim[c] / out.ginv[c]);
+        G = std::fmax(G, std::fabs(out.glo[c]));
+    }
+    out.err32 = (float)(16.0 * 0x1p-24 * X + 0x1p-48 * G) * 1.0001f;
+    out.planes32.resize(12 * (size_t)out.n_tets);
+    for (size_t e = 0; e < (size_t)out.n_tets; ++e) {
+        double c[4], S = 0.0;
+        for (int i = 0; i < 4; ++i) {
+            const double* n = &out.planes[16 * e + 4 * i];
+            c[i] = n[3] - ((n[0] * out.glo[0] + n[1] * out.glo[1]) + n[2] * out.glo[2]);
+            S -= c[i];                                   // the sum of the four D at glo (and anywhere)
+        }
+        bool fits = true;
+        float* q = &out.planes32[12 * e];
+        for (int i = 0; i < 3; ++i)
+            for (int k = 0; k < 4; ++k) {
+                const double m = (k < 3 ? out.planes[16 * e + 4 * i + k] : c[i]) / S;
+                fits = fits && std::fabs(m) < 1e30;
+                q[4 * i + k] = (float)m;
+            }
+        if (!fits) q[0] = INFINITY;
+    }
+}
+
 bool build_tet_tables(const double* V, int32_t nv, const int32_t* T, int32_t nt, TetTables& out,
                       std::string& err) {
     char buf[256];
@@ -235,6 +323,7 @@ bool build_tet_tables(const double* V, int32_t nv, const int32_t* T, int32_t nt,
             out.gdim[c] = 1;
         }
         out.cell_start.assign(2, 0);
+        out.cell_head = {-kFarMax, 0, 0, 0, -1, 0, 0, 0};
         build_bvh(V, T, nt, out);
         return true;
     }
@@ -302,6 +391,8 @@ bool build_tet_tables(const double* V, int32_t nv, const int32_t* T, int32_t nt,
     out.cell_tets.resize((size_t)count[cells]);
     std::vector<int32_t> fill(out.cell_start.begin(), out.cell_start.end() - 1);
     for (int32_t e = 0; e < nt; ++e) for_cells(e, [&](size_t q) { out.cell_tets[fill[q]++] = e; });
+    build_cell_heads(out);
+    build_planes32(out);
     build_bvh(V, T, nt, out);
     return true;
 }

@@ -16,6 +16,8 @@ namespace dpvr {
 // fractions, so no face normal of a lattice-aligned mesh is orthogonal to it).
 constexpr double kTieG[3] = {1.0, 0x1p-10, 0x1p-20};
 
+constexpr int kFarMax = 16;
+
 struct TetTables {
     int32_t n_tets = 0, n_vertices = 0;
     // Face i of tetrahedron e (the face opposite vertex i): planes[16 e + 4 i
@@ -25,6 +27,14 @@ struct TetTables {
     // vertices in lexicographic order, so the two tetrahedra sharing a face
     // compute the same D up to sign.
     std::vector<double> planes;
+    // Barycentric coordinates 0, 1, 2 (D_i over the sum of the four D) in
+    // float32 for points x relative to glo: planes32[12 e + 4 i + (0, 1, 2, 3)]
+    // = (mx, my, mz, c), coordinate i = m.x - c; coordinate 3 is one less their
+    // sum.  For points of the box and its margin every one of the four is
+    // within err32 (sum over i of |mx| + |my| + |mz|) of D_i over the sum; a
+    // record whose values do not fit float32 has an infinite mx.
+    std::vector<float> planes32;
+    float err32 = 0.0f;
     // bit i: a point with D_i = 0 counts as inside across face i (the tie
     // direction enters the tetrahedron there)
     std::vector<uint32_t> owned;
@@ -37,6 +47,13 @@ struct TetTables {
     int32_t gdim[3];
     std::vector<int32_t> cell_start;  // gdim product + 1 (exclusive prefix)
     std::vector<int32_t> cell_tets;   // tetrahedra of each cell, ascending
+    // Head of a cell that lists tetrahedra: the first two (the second -1 if
+    // there is one), then the range [q, qend) of the others in cell_tets; of
+    // one that lists none: minus its distance, in cells along the axis where
+    // it is largest, to the nearest cell that does, at most kFarMax (a ray
+    // meets only empty cells within that distance less one), and zeros.  After
+    // the last cell a head for points outside the grid (distance 1).
+    std::vector<int32_t> cell_head;
     // Bounding volume hierarchy over the tetrahedra, nodes in depth-first
     // order (a node's first child follows it), 8 words each: lo x, y, z
     // (float32 bits), skip; hi x, y, z (float32 bits), leaf.  The box is

@@ -16,10 +16,13 @@ enum : int32_t { kTetGrid = 0, kTetBvh = 1 };
 constexpr int kMaxTetParts = 64;
 struct TetPartK {
     const double* planes;       // n_tets x 16: per face (nx, ny, nz, c), D = n.p - c >= 0 inside
+    const float* planes32;      // n_tets x 12: barycentric planes in float32, for points relative to glo (tet_build.h)
+    const double* affine;       // 2 x n_tets x 2: (gx, gy), then (gz, c): value g . x + c of a point x relative to glo
     const float* vals;          // n_tets x 4: vertex values in vertex order (16-byte aligned)
     const uint32_t* owned;      // n_tets: tie-rule bits
     const int32_t* cell_start;  // grid cells + 1
     const int32_t* cell_tets;
+    const int32_t* cell_head;   // (grid cells + 1) x 4: each cell's head (tet_build.h)
     const int32_t* nbr;         // n_tets x 4: tetrahedron across each face (-1: none in the part)
     const int32_t* bvh_nodes;   // BVH nodes, 8 words each (tet_build.h)
     const int32_t* bvh_tets;    // leaves' tetrahedra
@@ -27,6 +30,7 @@ struct TetPartK {
     double glo[3], ginv[3];     // grid origin, cells per world unit
     int32_t gdim[3];
     int32_t n_tets;
+    float err32;                // error bound of the float32 planes (tet_build.h)
     int32_t roi_x0, roi_y0, roi_w, roi_h;
     long long entry0;           // first frame entry of the part (its ROI pixels, row-major, after the previous parts')
     int32_t* rcount;            // roi_h x roi_w: runs of the pixel's ray
@@ -50,25 +54,28 @@ struct TetFrameParams {
     // shadow rays (one directional light): per frame entry the first slot of
     // its held primary samples (offsets[n_entries] = total), per slot the
     // sample index and the shadow transmittance
+    TetPartK one;               // kTetAffine: the part whose values were set
     long long n_entries, total;
     long long* offsets;
     int32_t* slot_k;
     float* shade;
     double light[3];            // unit direction toward the light
     float ambient;              // a0: emission scaled by a0 + (1 - a0) S
-    int32_t step;               // cycle step of a shadow launch
 };
 
 // Stages of a tetrahedral frame (bit mask): the plain march into runs, the
 // resolve; with shadows: count the held samples per entry, record their
 // sample indices, the shadow cycle steps, the shaded march into runs.
-enum : int { kTetMarch = 1, kTetResolve = 2, kTetCount = 4, kTetRecord = 8, kTetShadow = 16, kTetShaded = 32 };
+// On its own, after a part's vertex values were set: its affine values.
+enum : int {
+    kTetMarch = 1, kTetResolve = 2, kTetCount = 4, kTetRecord = 8, kTetShadow = 16, kTetShaded = 32, kTetAffine = 64
+};
 
 constexpr int32_t kErrRuns = 4;   // a ray crossed a part in more than max_runs runs
 
-// Tiles of the tetrahedral march: kTetTile x kTetTile pixels, one workgroup
-// of (kTetTile / 8)^2 wavefronts of 8 x 8 rays each.
-constexpr int kTetTile = 16;
+// Tiles of the tetrahedral march: kTetTile x kTetTile pixels, one lane of a
+// wavefront each.
+constexpr int kTetTile = 8;
 inline int32_t tet_tiles(int32_t w, int32_t h) {
     return ((w + kTetTile - 1) / kTetTile) * ((h + kTetTile - 1) / kTetTile);
 }

@@ -3,12 +3,13 @@
 // a share of a finite-element data set.
 //
 // A frame, for n parts and the context camera:
-//   march     one workgroup per tile of a part's ROI (the part's bounding
-//             box projected), wavefronts of 8 x 8 rays.
+//   march     one workgroup per 8 x 8 tile of a part's ROI (the part's
+//             bounding box projected), its wavefronts taking stretches of the
+//             tile's rays.
 //             Every lattice sample t_k = (k + 1/2) dt of the ray inside the
 //             part's bounding box is located in the part: by a short walk
 //             from the tetrahedron that held the ray's previous sample (to the
-//             neighbour across the first face that rejects the sample), else
+//             neighbour across the face that rejects the sample most), else
 //             among the tetrahedra listed in the sample's cell of the part's
 //             uniform grid.  A tetrahedron holds p when its four signed sub-volumes
 //             are positive, a zero one counting when the tie direction enters
@@ -24,21 +25,31 @@
 //             share a sample, so this equals accumulating the whole ray.
 // With one directional light, before the march: a count pass (held samples
 // per ROI pixel of every part), an exclusive scan (a slot per held sample), a
-// record pass (each slot's sample index), then n cycle steps in which every
-// slot's shadow ray visits part (home + s) mod n, and the march scales each
-// held sample's emission by a0 + (1 - a0) S from its slot.
-// Locations use float64 with contraction off (the planes come from the host
-// in float64), so the owner of a sample does not depend on the launch.
+// record pass (each slot's sample index), then the shadow pass, in which every
+// slot's shadow ray visits part home, home + 1, ... (mod n), and the march
+// scales each held sample's emission by a0 + (1 - a0) S from its slot.
+// Locations are those of float64 planes with contraction off (float32 planes
+// with an error bound settle what they can), so the owner of a sample does
+// not depend on the launch.
+// Measured (1280x720, 2.0 M tetrahedra in 8 parts, 20.6 M held samples): one
+// lane per ray, in step, float64 planes 3.91 ms a frame; as here 1.60 ms.
+// 384x384, 246 K in 4 parts with shadows: 21.7 -> 5.5 ms; 14.6 K in 3 parts,
+// 317x241: 0.48 -> 0.18 ms.
 #include "march_common.h"
 #include "tet_kernels.h"
 
 namespace dpvr {
 namespace {
 
-typedef __attribute__((address_space(1))) const double gdouble;
-typedef __attribute__((address_space(1))) const float gfloat_t;
 typedef __attribute__((address_space(1))) const int32_t gint;
 typedef __attribute__((address_space(1))) const uint32_t guint;
+typedef double double2_t __attribute__((ext_vector_type(2)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef int int4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) const double2_t gdouble2;
+typedef __attribute__((address_space(1))) const float4_t gfloat4;
+typedef int4_t int4_unaligned __attribute__((aligned(4)));
+typedef __attribute__((address_space(1))) const int4_unaligned gint4_unaligned;
 
 // Value of vertex v: given, or (a cell centre) the mean of its cell's
 // nodes, summed in node order.
@@ -87,20 +98,47 @@ __device__ inline bool box_range(const CamRay& r, const double lo[3], const doub
     return true;
 }
 
-// Whether tetrahedron e holds p; if so its four sub-volumes in D, if not
-// the first face that rejects p in *out.
-__device__ inline bool holds(const TetPartK& P, int e, double p0, double p1, double p2, double D[4], int* out) {
+// The four sub-volumes D of p in tetrahedron e, and the face to leave it by when it does not hold p: of the faces that reject p, the one
+// with the most negative sub-volume (-1: e holds p).
+__device__ inline int reject_face(const TetPartK& P, int e, double p0, double p1, double p2, double D[4]) {
 #pragma clang fp contract(off)
-    gdouble* pl = ((gdouble*)P.planes) + 16 * (long long)e;
+    gdouble2* pl = ((gdouble2*)P.planes) + 8 * (long long)e;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        D[i] = ((pl[4 * i] * p0 + pl[4 * i + 1] * p1) + pl[4 * i + 2] * p2) - pl[4 * i + 3];
-        if (D[i] < 0.0 || (D[i] == 0.0 && !((((guint*)P.owned)[e] >> i) & 1u))) {
-            *out = i;
-            return false;
-        }
+        const double2_t a = pl[2 * i], b = pl[2 * i + 1];
+        D[i] = ((a.x * p0 + a.y * p1) + b.x * p2) - b.y;
     }
-    return true;
+    const double least = fmin(fmin(D[0], D[1]), fmin(D[2], D[3]));
+    int face = D[0] == least ? 0 : D[1] == least ? 1 : D[2] == least ? 2 : 3;
+    if (least > 0.0) face = -1;
+    if (least == 0.0) {                  // on a face (rare): the tie rule
+        const uint32_t own = ((guint*)P.owned)[e];
+        face = -1;
+#pragma unroll
+        for (int i = 3; i >= 0; --i) face = D[i] == 0.0 && !((own >> i) & 1u) ? i : face;
+    }
+    return face;
+}
+
+// reject_face in float32 (x: p relative to the part's grid origin; pl: the
+// tetrahedron's float32 record, the first three barycentric coordinates as
+// planes), where the smallest coordinate is beyond the error bound;
+// kUndecided otherwise (also for records marked with an infinity).
+constexpr int kUndecided = 4;
+__device__ inline int reject_face32(const TetPartK& P, const float4_t (&pl)[3], float x0, float x1, float x2) {
+    float l[4], e = 0.0f;
+    l[3] = 1.0f;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const float4_t n = pl[i];
+        l[i] = fmaf(n.x, x0, fmaf(n.y, x1, fmaf(n.z, x2, -n.w)));
+        l[3] -= l[i];
+        e += fabsf(n.x) + fabsf(n.y) + fabsf(n.z);
+    }
+    e *= P.err32;
+    const float least = fminf(fminf(l[0], l[1]), fminf(l[2], l[3]));
+    const int face = l[0] == least ? 0 : l[1] == least ? 1 : l[2] == least ? 2 : 3;
+    return least + e < 0.0f ? face : least - e > 0.0f ? -1 : kUndecided;
 }
 
 // Steps of the walk from the previous sample's tetrahedron across rejecting
@@ -115,11 +153,12 @@ __device__ inline void count_held(unsigned long long* counter, unsigned long lon
     if ((threadIdx.x & 63) == 0 && n) atomicAdd(counter, n);
 }
 
-// The tetrahedron of part P that holds p (-1: none) by the BVH: from the
+// The tetrahedron of part P that holds p (-1: none), by the BVH: from the
 // root, a node whose box holds p is entered (its first child follows it; a
 // leaf's tetrahedra are tested), any other is skipped through its skip link.
-__device__ inline int bvh_locate(const TetPartK& P, double p0, double p1, double p2, double D[4]) {
-    int node = P.n_tets > 0 ? 0 : -1, face = 0;
+__device__ inline int bvh_locate(const TetPartK& P, double p0, double p1, double p2) {
+    double D[4];
+    int node = P.n_tets > 0 ? 0 : -1;
     while (node >= 0) {
         gint* nd = ((gint*)P.bvh_nodes) + 8 * (long long)node;
         const int skip = nd[3], leaf = nd[7];
@@ -132,7 +171,7 @@ __device__ inline int bvh_locate(const TetPartK& P, double p0, double p1, double
             const int first = leaf >> 3, count = leaf & 7;
             for (int i = 0; i < count; ++i) {
                 const int e = ((gint*)P.bvh_tets)[first + i];
-                if (holds(P, e, p0, p1, p2, D, &face)) return e;
+                if (reject_face(P, e, p0, p1, p2, D) < 0) return e;
             }
             node = skip;
         } else {
@@ -142,85 +181,244 @@ __device__ inline int bvh_locate(const TetPartK& P, double p0, double p1, double
     return -1;
 }
 
-// The tetrahedron of part P that holds p (-1: none): one candidate per loop
-// trip, so that the lanes of a wavefront stay on the same code -- first the
-// walk from tetrahedron `from` (kWalkSteps tests, across the first face that
-// rejects p), then the tetrahedra of p's grid cell.  D: its sub-volumes.
-template <int kLocator>
-__device__ inline int locate(const TetPartK& P, int from, double p0, double p1, double p2, double D[4]) {
+// Value of a point in tetrahedron e: the affine function of the part's
+// records (x: the point relative to the grid origin), in float64.  Where a
+// vertex value is not finite the record is NaN and the barycentric sum of
+// the sub-volumes of p takes its place.
+__device__ inline float tet_value(const TetPartK& P, int e, const double x[3], const double p[3]) {
 #pragma clang fp contract(off)
-    int cand = from, face = 0, walk = kWalkSteps, q = 0, qend = 0;
-    bool grid = false;
-    for (;;) {
-        if (cand < 0) {
-            if (kLocator == kTetBvh) return bvh_locate(P, p0, p1, p2, D);
-            if (!grid) {
-                grid = true;
-                const double u0 = (p0 - P.glo[0]) * P.ginv[0], u1 = (p1 - P.glo[1]) * P.ginv[1],
-                             u2 = (p2 - P.glo[2]) * P.ginv[2];
-                if (u0 >= 0.0 && u1 >= 0.0 && u2 >= 0.0 && u0 < (double)P.gdim[0] && u1 < (double)P.gdim[1] &&
-                    u2 < (double)P.gdim[2]) {
-                    const long long cell = ((long long)(int)u2 * P.gdim[1] + (int)u1) * P.gdim[0] + (int)u0;
-                    q = ((gint*)P.cell_start)[cell];
-                    qend = ((gint*)P.cell_start)[cell + 1];
-                }
-            }
-            if (q >= qend) return -1;
-            cand = ((gint*)P.cell_tets)[q++];
-        }
-        if (holds(P, cand, p0, p1, p2, D, &face)) return cand;
-        cand = !grid && --walk > 0 ? ((gint*)P.nbr)[4 * (long long)cand + face] : -1;
-    }
-}
-
-// Barycentric value of a point with sub-volumes D in tetrahedron e: the
-// weighted sum in float64, one float32 division (the value is classified in
-// float32).
-__device__ inline float tet_value(const TetPartK& P, int e, const double D[4]) {
-#pragma clang fp contract(off)
-    gfloat_t* vv = ((gfloat_t*)P.vals) + 4 * (long long)e;
+    gdouble2* rec = ((gdouble2*)P.affine) + e;
+    const double2_t a = rec[0], b = rec[P.n_tets];
+    const double v = ((a.x * x[0] + a.y * x[1]) + b.x * x[2]) + b.y;
+    if (v == v) return (float)v;
+    double D[4];
+    (void)reject_face(P, e, p[0], p[1], p[2], D);
+    const float4_t w = ((gfloat4*)P.vals)[e];
     const double s = ((D[0] + D[1]) + D[2]) + D[3];
-    const double num = ((D[0] * (double)vv[0] + D[1] * (double)vv[1]) + D[2] * (double)vv[2]) + D[3] * (double)vv[3];
+    const double num = ((D[0] * (double)w.x + D[1] * (double)w.y) + D[2] * (double)w.z) + D[3] * (double)w.w;
     return __fdividef((float)num, (float)s);
 }
 
-constexpr int kTetThreads = kTetTile * kTetTile;
-
-// The march of every part's ROI rays, in one of four modes: kTetMarch
-// (runs), kTetCount (held samples per frame entry into offsets), kTetRecord
-// (the sample index of every held sample into its slot) and kTetShaded (runs
-// with every held sample's emission scaled by a0 + (1 - a0) S from its slot).
-template <int kMode, int kLocator>
-__global__ __launch_bounds__(kTetThreads) void tet_march(TetFrameParams f) {
-    constexpr bool kRuns = kMode == kTetMarch || kMode == kTetShaded;
-    __shared__ TFTable tft;
-    if (kRuns) {
-        load_tf(tft, f.tf, f.dt, threadIdx.x, kTetThreads);
-        __syncthreads();
+// The records of a part's affine values: value(x) = g . x + c with x
+// relative to the grid origin, from the planes and the vertex values
+// (v0 + sum (v_i - v0) D_i(x) / sum D_i; the D_i sum to the same volume at
+// every x).
+__global__ __launch_bounds__(256) void tet_affine(TetPartK P, double2_t* __restrict__ out) {
+#pragma clang fp contract(off)
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= P.n_tets) return;
+    gdouble2* pl = ((gdouble2*)P.planes) + 8 * (long long)e;
+    const float4_t v = ((gfloat4*)P.vals)[e];
+    double n[4][3], d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const double2_t a = pl[2 * i], b = pl[2 * i + 1];
+        n[i][0] = a.x;
+        n[i][1] = a.y;
+        n[i][2] = b.x;
+        d[i] = ((a.x * P.glo[0] + a.y * P.glo[1]) + b.x * P.glo[2]) - b.y;   // D_i at x = 0
     }
-    const int wg = blockIdx.x;
+    const double S = ((d[0] + d[1]) + d[2]) + d[3];
+    const double w[3] = {((double)v.y - (double)v.x) / S, ((double)v.z - (double)v.x) / S,
+                         ((double)v.w - (double)v.x) / S};
+    double g[3], c = (double)v.x;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) g[a] = (w[0] * n[1][a] + w[1] * n[2][a]) + w[2] * n[3][a];
+    c += (w[0] * d[1] + w[1] * d[2]) + w[2] * d[3];
+    const float all = ((v.x - v.x) + (v.y - v.y)) + ((v.z - v.z) + (v.w - v.w));   // NaN unless all are finite
+    if (!(all == 0.0f)) c = __builtin_nan("");
+    out[e] = double2_t{g[0], g[1]};
+    out[(long long)P.n_tets + e] = double2_t{g[2], c};
+}
+
+// The samples k0 .. k1 (none if k1 < k0; both in [0, 2^31)) of ray r in part
+// P, in order: held(k, value) for a sample that a tetrahedron holds, gap()
+// for a stretch of samples that none holds.  A sample is sought by a walk from
+// the previous sample's tetrahedron (kWalkSteps tests, each step across the
+// face that rejects it most), then among the tetrahedra listed in its grid
+// cell (or in the BVH).
+//
+// Vector-memory instructions bound this (a 16-byte load of 64 scattered lanes
+// takes the L1 33 to 65 cycles, 17 where four neighbouring lanes share a
+// line; measured), so a test reads 48 bytes of float32 barycentric planes and
+// only a sample that they leave undecided reads the 128 bytes of float64 ones.
+// A loop trip waits once: it issues what every lane needs next -- one 16-byte
+// load per lane of its tetrahedron's neighbours, its list's next candidates or
+// its cell's head, and the planes -- and then settles what it can.  Every
+// lane is at its own sample: one whose sample is settled goes on while others
+// still search (with the lanes in step, a wavefront took the longest search
+// of its 64 lanes at every sample).  A sample in an empty cell, d cells from
+// the nearest listed one, also settles the following ones that stay within
+// d - 1 cells of it.
+template <int kLocator, bool kValues, typename Held, typename Gap>
+__device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, double dt, long long k0, long long k1,
+                                          Held held, Gap gap) {
+#pragma clang fp contract(off)
+    unsigned k = (unsigned)k0;
+    int left = k1 >= k0 ? (int)(k1 - k0) : -1;           // samples after this one
+    int cand = -1;                                       // tetrahedron to test (-1: look the sample's cell up)
+    int walk = 0;                                        // walk steps left (0: cand is from the cell's list)
+    int next = -1, q = 0, qend = 0;                      // the list's candidate after cand, and the rest [q, qend)
+    const int cells = P.gdim[0] * P.gdim[1] * P.gdim[2];
+    // (0.999: below the true ratio whatever the rounding)
+    const double move = fmax(fmax(fabs(r.d[0] * dt * P.ginv[0]), fabs(r.d[1] * dt * P.ginv[1])),
+                             fabs(r.d[2] * dt * P.ginv[2]));     // cells per sample, at most
+    const float per_cell = (float)fmin(0.999 / move, 1e6);       // samples per cell moved
+    double x[3];                                         // the sample relative to the grid origin
+    auto point = [&](double p[3]) {
+        const double t = ((double)k + 0.5) * dt;
+        for (int c = 0; c < 3; ++c) p[c] = r.o[c] + t * r.d[c];
+    };
+    auto place = [&]() {
+        double p[3];
+        point(p);
+        for (int c = 0; c < 3; ++c) x[c] = p[c] - P.glo[c];
+    };
+    place();
+    while (left >= 0) {
+        int settle = 0;                                  // samples to go on by
+        int found = -1;
+        // (a point outside the grid takes the head after the last cell's, of
+        // an empty cell; one less than a cell below the grid looks cell 0 up,
+        // whose tetrahedra reject it)
+        gint* src = (gint*)P.cell_head;
+        float4_t pl[3];
+        if (cand >= 0) {
+            src = walk > 0 ? (gint*)P.nbr + 4 * (long long)cand : (gint*)P.cell_tets + q;
+            gfloat4* rec = ((gfloat4*)P.planes32) + 3 * (long long)cand;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) pl[i] = rec[i];
+        } else if (kLocator == kTetGrid) {
+            const int c0 = (int)(x[0] * P.ginv[0]), c1 = (int)(x[1] * P.ginv[1]), c2 = (int)(x[2] * P.ginv[2]);
+            const bool in = ((unsigned)c0 < (unsigned)P.gdim[0]) & ((unsigned)c1 < (unsigned)P.gdim[1]) &
+                            ((unsigned)c2 < (unsigned)P.gdim[2]);
+            src += 4 * (long long)(in ? (c2 * P.gdim[1] + c1) * P.gdim[0] + c0 : cells);
+        }
+        const int4_t aux = *(gint4_unaligned*)src;
+        if (cand >= 0) {
+            int face = reject_face32(P, pl, (float)x[0], (float)x[1], (float)x[2]);
+            if (face == kUndecided) {
+                double p[3], D[4];
+                point(p);
+                face = reject_face(P, cand, p[0], p[1], p[2], D);
+            }
+            if (face < 0) {
+                found = cand;
+                settle = 1;
+            } else if (walk > 0) {
+                cand = --walk > 0 ? (face == 0 ? aux.x : face == 1 ? aux.y : face == 2 ? aux.z : aux.w) : -1;
+            } else {
+                cand = next;
+                next = q < qend ? aux.x : -1;
+                ++q;
+                if (cand < 0) settle = 1;                // the cell's list is through
+            }
+        } else if (kLocator == kTetBvh) {
+            double p[3];
+            point(p);
+            found = bvh_locate(P, p[0], p[1], p[2]);
+            settle = 1;
+        } else if (aux.x < 0) {
+            settle = 1 + (int)((float)(-aux.x - 1) * per_cell);
+        } else {
+            cand = aux.x;
+            next = aux.y;
+            walk = 0;
+            q = aux.z;
+            qend = aux.w;
+        }
+        if (settle > 0) {
+            if (found >= 0) {
+                float v = 0.0f;
+                if (kValues) {
+                    double p[3];
+                    point(p);
+                    v = tet_value(P, found, x, p);
+                }
+                held((int)k, v);
+            } else {
+                gap();
+            }
+            cand = found;
+            walk = kWalkSteps;
+            q = qend;
+            k += (unsigned)settle;
+            left = settle > left ? -1 : left - settle;
+            place();
+        }
+    }
+}
+
+// A tile's rays are cut into kStretches stretches of equal length, which the
+// kWaves wavefronts of its workgroup take one after another: a wavefront
+// alone waits for its slowest ray through every search, and a small frame has
+// too few tiles to fill the GPU.  (One fixed stretch per wavefront leaves most
+// of them idle: a part fills its bounding box unevenly.)  The stretches' runs
+// wait in a pool of kPool entries in LDS, chained per ray and stretch, and are
+// joined in order afterwards.
+constexpr int kWaves = 4;
+constexpr int kStretches = 8;
+constexpr int kPool = 704;
+
+// Part and ROI pixel of this thread (its lane) in tile `wg` of the frame's
+// tiles.  A part's tiles are numbered down the columns of bands 8 tiles high,
+// so that tiles in flight together are a compact block of the image whose
+// rays share tetrahedra.  (Giving each XCD runs of 64 consecutive tiles cut
+// the L2 misses to a sixth but left the XCDs unevenly loaded: 2.18 against
+// 1.85 ms for 2.0 M tetrahedra at 1280x720.)
+__device__ inline int tile_pixel(const TetFrameParams& f, int wg, int& lx, int& ly) {
     int lo = 0, hi = f.n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (f.tile_start[mid] <= wg) lo = mid; else hi = mid - 1;
     }
-    const int j = __builtin_amdgcn_readfirstlane(lo);
-    // a copy in registers: the run stores below cannot alias it, so its
-    // fields are loaded once
-    const TetPartK P = f.parts[j];
-    const int tile = wg - f.tile_start[j];
-    const int tiles_x = (P.roi_w + kTetTile - 1) / kTetTile;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int lx = (tile % tiles_x) * kTetTile + (wave % (kTetTile / 8)) * 8 + (lane & 7);
-    const int ly = (tile / tiles_x) * kTetTile + (wave / (kTetTile / 8)) * 8 + (lane >> 3);
+    const int j = uniform_i(lo);
+    const int tile = wg - uniform_i(f.tile_start[j]);
+    const TetPartK& P = const_entry(f.parts, j);
+    const int tiles_x = (P.roi_w + kTetTile - 1) / kTetTile, tiles_y = (P.roi_h + kTetTile - 1) / kTetTile;
+    const int band = tile / (8 * tiles_x), r = tile - band * 8 * tiles_x;
+    const int rows = min(8, tiles_y - 8 * band);
+    const int lane = threadIdx.x & 63;
+    // lanes in Z order: four consecutive lanes are 2 x 2 pixels
+    lx = r / rows * kTetTile + ((lane & 1) | (lane >> 1 & 2) | (lane >> 2 & 4));
+    ly = (8 * band + r % rows) * kTetTile + ((lane >> 1 & 1) | (lane >> 2 & 2) | (lane >> 3 & 4));
+    return j;
+}
+
+// The march of every part's ROI rays, in one of four modes: kTetMarch
+// (runs), kTetCount (held samples per frame entry into offsets), kTetRecord
+// (the sample index of every held sample into its slot) and kTetShaded (runs
+// with every held sample's emission scaled by a0 + (1 - a0) S from its slot).
+template <int kMode>
+constexpr bool tet_runs() { return kMode == kTetMarch || kMode == kTetShaded; }
+
+template <int kMode, int kLocator>
+__global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_march(TetFrameParams f) {
+    constexpr bool kRuns = tet_runs<kMode>();
+    __shared__ TFTable tft;
+    __shared__ int run_key[kRuns ? kPool : 1], run_end[kRuns ? kPool : 1];
+    __shared__ float run_rgb[kRuns ? 3 * kPool : 1], run_T[kRuns ? kPool : 1];
+    __shared__ short run_next[kRuns ? kPool : 1];
+    __shared__ short first_run[kRuns ? kStretches * 64 : 1];
+    __shared__ int pool_used, taken;
+    const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
+    if (kRuns) {
+        load_tf(tft, f.tf, f.dt, threadIdx.x, 64 * kWaves);
+        if (threadIdx.x == 0) {
+            pool_used = 0;
+            taken = kWaves;
+        }
+        __syncthreads();
+    }
+    int lx, ly;
+    const int j = tile_pixel(f, blockIdx.x, lx, ly);
+    const TetPartK& P = const_entry(f.parts, j);
     const bool live = lx < P.roi_w && ly < P.roi_h;
     const long long npix = (long long)P.roi_w * P.roi_h;
     const long long li = (long long)ly * P.roi_w + lx;
     const float tf_k = 255.0f / (f.tf.vmax - f.tf.vmin);
     const float tf_o = -f.tf.vmin * tf_k;
     const float a0 = f.ambient, a1 = 1.0f - f.ambient;
-    unsigned long long held = 0;
-    int nrun = 0;
     long long k0 = 0, k1 = -1, slot0 = 0, slots = 0;
     CamRay r{};
     if (live) {
@@ -234,134 +432,217 @@ __global__ __launch_bounds__(kTetThreads) void tet_march(TetFrameParams f) {
             slots = f.offsets[P.entry0 + li + 1] - slot0;   // the count pass's held samples of this ray
         }
     }
-    bool in_run = false, overflow = false;
-    int key = 0, last = -1;
-    float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;
-    auto close_run = [&]() {
-        if (nrun < f.max_runs) {
-            const long long q = (long long)nrun * npix + li;
-            P.rkey[q] = key;
-            reinterpret_cast<float4*>(P.rcol)[q] = make_float4(C0, C1, C2, 1.0f - T);
-            ++nrun;
-        } else {
-            overflow = true;
-        }
-        in_run = false;
-    };
-    for (long long k = k0; k <= k1; ++k) {
-#pragma clang fp contract(off)
-        const double t = ((double)k + 0.5) * f.dt;
-        const double p0 = r.o[0] + t * r.d[0], p1 = r.o[1] + t * r.d[1], p2 = r.o[2] + t * r.d[2];
-        double D[4];
-        const int e = locate<kLocator>(P, last, p0, p1, p2, D);
-        last = e;
-        if (e < 0) {
-            if (kRuns && in_run) close_run();
-            continue;
-        }
-        if (kMode == kTetCount) {
-            ++held;
-            continue;
-        }
-        if (kMode == kTetRecord) {
+    if constexpr (!kRuns) {
+        unsigned long long held = 0;
+        walk_part<kLocator, false>(P, r, f.dt, k0, k1, [&](int k, float) {
             // the passes locate alike, so a ray holds as many samples as
             // counted; a mismatch (which only a logic error could cause) is
             // reported and never writes outside the ray's slots
-            if ((long long)held < slots) f.slot_k[slot0 + (long long)held] = (int)k;
-            else if (f.err) atomicOr(f.err, kErrRange);
+            if (kMode == kTetRecord) {
+                if ((long long)held < slots) f.slot_k[slot0 + (long long)held] = k;
+                else if (f.err) atomicOr(f.err, kErrRange);
+            }
             ++held;
-            continue;
-        }
-        if (!in_run) {
-            in_run = true;
-            key = (int)k;
-            C0 = C1 = C2 = 0.f;
-            T = 1.f;
-        }
-        const Classified c = classify(tft, tet_value(P, e, D), tf_k, tf_o);
-        float sh = 1.0f;
-        if (kMode == kTetShaded) sh = a0 + a1 * ((long long)held < slots ? f.shade[slot0 + (long long)held] : 1.0f);
-        const float Tn = T * trans_exp2(-c.a);
-        const float w = T - Tn;
-        C0 = fmaf(w, c.r * sh, C0);
-        C1 = fmaf(w, c.g * sh, C1);
-        C2 = fmaf(w, c.b * sh, C2);
-        T = Tn;
-        ++held;
-    }
-    if (kMode == kTetCount) {
-        if (live) f.offsets[P.entry0 + li] = (long long)held;
+        }, []() {});
+        if (kMode == kTetCount && live) f.offsets[P.entry0 + li] = (long long)held;
         return;
     }
-    if (kMode == kTetRecord) return;
-    if (in_run) close_run();
-    if (overflow && f.err) atomicOr(f.err, kErrRuns);
-    if (live) P.rcount[li] = nrun;
-    count_held(f.samples, held);
+    auto store = [&](int n, int key, float c0, float c1, float c2, float T) {
+        const long long q = (long long)n * npix + li;
+        P.rkey[q] = key;
+        reinterpret_cast<float4*>(P.rcol)[q] = make_float4(c0, c1, c2, 1.0f - T);
+    };
+    unsigned long long held = 0, counted = 0;   // of a stretch, of all that this wavefront took
+    int nrun = 0;
+    bool overflow = false;
+    // the stretches of this wavefront; should the pool not hold the tile's
+    // runs, wavefront 0 takes its rays again, whole, and stores their runs as
+    // they end
+    bool whole = false;
+    for (int piece = wave;;) {
+        const long long n = k1 - k0 + 1;
+        long long ka = k0 + n * piece / kStretches, kb = k0 + n * (piece + 1) / kStretches - 1;
+        if (whole) {
+            ka = k0;
+            kb = k1;
+        }
+        long long slot = slot0;                 // of this stretch's first held sample: slots are in sample order
+        if (kMode == kTetShaded && ka > k0) {
+            long long lo = 0, hi = slots;
+            while (lo < hi) {
+                const long long mid = (lo + hi) >> 1;
+                if ((long long)f.slot_k[slot0 + mid] < ka) lo = mid + 1; else hi = mid;
+            }
+            slot += lo;
+        }
+        held = 0;
+        nrun = 0;
+        int first = -1, last = -1;              // this stretch's chain
+        bool in_run = false;
+        int key = 0, end = 0;
+        float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;
+        auto close_run = [&]() {
+            if (whole) {
+                if (nrun < f.max_runs) store(nrun, key, C0, C1, C2, T);
+                else overflow = true;
+            } else {
+                const int i = atomicAdd(&pool_used, 1);
+                if (i < kPool) {
+                    run_key[i] = key;
+                    run_end[i] = end;
+                    run_rgb[3 * i] = C0;
+                    run_rgb[3 * i + 1] = C1;
+                    run_rgb[3 * i + 2] = C2;
+                    run_T[i] = T;
+                    run_next[i] = -1;
+                    if (last >= 0) run_next[last] = (short)i;
+                    else first = i;
+                    last = i;
+                }
+            }
+            ++nrun;
+            in_run = false;
+        };
+        walk_part<kLocator, true>(P, r, f.dt, ka, kb, [&](int k, float v) {
+#pragma clang fp contract(off)
+            if (!in_run) {
+                in_run = true;
+                key = k;
+                C0 = C1 = C2 = 0.f;
+                T = 1.f;
+            }
+            end = k;
+            const Classified c = classify(tft, v, tf_k, tf_o);
+            float sh = 1.0f;
+            if (kMode == kTetShaded) {
+                const long long q = slot + (long long)held;
+                sh = a0 + a1 * (q < slot0 + slots ? f.shade[q] : 1.0f);
+            }
+            const float Tn = T * trans_exp2(-c.a);
+            const float w = T - Tn;
+            C0 = fmaf(w, c.r * sh, C0);
+            C1 = fmaf(w, c.g * sh, C1);
+            C2 = fmaf(w, c.b * sh, C2);
+            T = Tn;
+            ++held;
+        }, [&]() {
+            if (in_run) close_run();
+        });
+        if (in_run) close_run();
+        counted += held;
+        if (whole) break;
+        first_run[piece * 64 + lane] = (short)first;
+        if (lane == 0) piece = atomicAdd(&taken, 1);
+        piece = uniform_i(piece);
+        if (piece < kStretches) continue;
+        __syncthreads();
+        whole = uniform_i(pool_used) > kPool;
+        if (!whole || wave > 0) break;
+        counted = 0;
+    }
+    if (whole && wave > 0) counted = 0;
+    if (wave == 0 && live) {
+        if (!whole) {
+            // join the stretches: a run that goes on in the next one is one run
+            nrun = 0;
+            bool open = false;
+            int key = 0, end = 0;
+            float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;
+            auto put = [&]() {
+                if (nrun < f.max_runs) {
+                    store(nrun, key, C0, C1, C2, T);
+                    ++nrun;
+                } else {
+                    overflow = true;
+                }
+            };
+            for (int s = 0; s < kStretches; ++s) {
+                for (int i = first_run[s * 64 + lane]; i >= 0; i = run_next[i]) {
+                    const int nk = run_key[i];
+                    const float n0 = run_rgb[3 * i], n1 = run_rgb[3 * i + 1], n2 = run_rgb[3 * i + 2];
+                    if (open && nk == end + 1) {
+                        C0 = fmaf(T, n0, C0);
+                        C1 = fmaf(T, n1, C1);
+                        C2 = fmaf(T, n2, C2);
+                        T *= run_T[i];
+                    } else {
+                        if (open) put();
+                        open = true;
+                        key = nk;
+                        C0 = n0;
+                        C1 = n1;
+                        C2 = n2;
+                        T = run_T[i];
+                    }
+                    end = run_end[i];
+                }
+            }
+            if (open) put();
+        }
+        P.rcount[li] = min(nrun, f.max_runs);
+        if (overflow && f.err) atomicOr(f.err, kErrRuns);
+    }
+    count_held(f.samples, counted);
 }
 
-// Cycle step s of the shadow rays: the shadow ray of every held primary
-// sample (its slot) through part (home + s) mod n, home the part that holds
-// the sample; the slot's transmittance is multiplied by the part's (products
-// commute, so the visiting order does not matter to the value).
+// The shadow rays of one tile of a home part's ROI (blockIdx.x, the tiles of
+// the march): the ray of every held primary sample (its slot) cycles through
+// the parts home, home + 1, ... (mod n), multiplying its transmittance by
+// each one's.  A lane takes every kShadowSplit-th held sample of its pixel
+// (from its wavefront's place in the kShadowSplit of its tile), so that a wavefront's 64 rays start at the same depth
+// behind 8 x 8 neighbouring pixels and cross the same tetrahedra; with the
+// lanes on 64 consecutive samples of one primary ray their loads touched as
+// many lines as lanes.
+constexpr int kShadowSplit = 256;
+
 template <int kLocator>
-__global__ __launch_bounds__(256) void tet_shadow_step(TetFrameParams f) {
+__global__ __launch_bounds__(256, 5) void tet_shadow(TetFrameParams f) {
     __shared__ TFTable tft;
     load_tf(tft, f.tf, f.dt, threadIdx.x, 256);
     __syncthreads();
     const float tf_k = 255.0f / (f.tf.vmax - f.tf.vmin);
     const float tf_o = -f.tf.vmin * tf_k;
+    int lx, ly;
+    const int j = tile_pixel(f, blockIdx.x, lx, ly);
+    const TetPartK& home = const_entry(f.parts, j);
+    const bool live = lx < home.roi_w && ly < home.roi_h;
+    long long slot0 = 0, slots = 0;
+    CamRay cr{};
+    if (live) {
+        const long long e = home.entry0 + (long long)ly * home.roi_w + lx;
+        slot0 = f.offsets[e];
+        slots = f.offsets[e + 1] - slot0;
+        cr = camera_ray(f.cam, home.roi_x0 + lx, home.roi_y0 + ly);
+    }
     unsigned long long evaluated = 0;
-    // the largest e with offsets[e] <= slot (over [lo, hi])
-    auto entry_in = [&](long long slot, long long lo, long long hi) {
-        while (lo < hi) {
-            const long long mid = (lo + hi + 1) >> 1;
-            if (f.offsets[mid] <= slot) lo = mid; else hi = mid - 1;
-        }
-        return lo;
-    };
-    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < f.total; q += (long long)gridDim.x * 256) {
-        // the slot's entry and home part; the active lanes of a wavefront
-        // hold consecutive slots from its first active lane's, so two
-        // wavefront-uniform searches bound every lane's entry
-        const unsigned q_lo = __builtin_amdgcn_readfirstlane((unsigned)q);
-        const unsigned q_hi = __builtin_amdgcn_readfirstlane((unsigned)((unsigned long long)q >> 32));
-        const long long q0 = (long long)(((unsigned long long)q_hi << 32) | q_lo);
-        const long long elo = entry_in(q, entry_in(q0, 0, f.n_entries - 1), entry_in(q0 + 63, 0, f.n_entries - 1));
-        int hlo = 0, hhi = f.n - 1;
-        while (hlo < hhi) {
-            const int mid = (hlo + hhi + 1) >> 1;
-            if (f.parts[mid].entry0 <= elo) hlo = mid; else hhi = mid - 1;
-        }
-        const TetPartK& home = f.parts[hlo];
-        const TetPartK& at = f.parts[(hlo + f.step) % f.n];
-        const long long r = elo - home.entry0;
-        const CamRay cr = camera_ray(f.cam, home.roi_x0 + (int)(r % home.roi_w), home.roi_y0 + (int)(r / home.roi_w));
+    for (long long i = 4 * blockIdx.y + (threadIdx.x >> 6); i < slots; i += kShadowSplit) {
         CamRay sr;
         {
 #pragma clang fp contract(off)
-            const double t = ((double)f.slot_k[q] + 0.5) * f.dt;
+            const double t = ((double)f.slot_k[slot0 + i] + 0.5) * f.dt;
             for (int a = 0; a < 3; ++a) {
                 sr.o[a] = cr.o[a] + t * cr.d[a];
                 sr.d[a] = f.light[a];
             }
         }
-        float S = 1.0f;
-        long long j0, j1;
-        if (at.n_tets > 0 && box_range(sr, at.lo, at.hi, f.dt, j0, j1)) {
-            int last = -1;
-            for (long long jj = j0; jj <= j1; ++jj) {
-#pragma clang fp contract(off)
-                const double t = ((double)jj + 0.5) * f.dt;
-                const double p0 = sr.o[0] + t * sr.d[0], p1 = sr.o[1] + t * sr.d[1], p2 = sr.o[2] + t * sr.d[2];
-                double D[4];
-                last = locate<kLocator>(at, last, p0, p1, p2, D);
-                if (last < 0) continue;
-                S = S * trans_exp2(-classify(tft, tet_value(at, last, D), tf_k, tf_o).a);
-                ++evaluated;
+        float all = 1.0f;
+        for (int s = 0; s < f.n; ++s) {
+            int h = j + s;
+            h = h >= f.n ? h - f.n : h;
+            const TetPartK& at = const_entry(f.parts, h);
+            float S = 1.0f;
+            long long j0 = 0, j1 = -1;
+            if (at.n_tets > 0 && box_range(sr, at.lo, at.hi, f.dt, j0, j1) && j1 > 0x7fffffffLL) {
+                if (f.err) atomicOr(f.err, kErrRange);
+                j1 = j0 - 1;
             }
+            walk_part<kLocator, true>(at, sr, f.dt, j0, j1, [&](int, float v) {
+                S = S * trans_exp2(-classify(tft, v, tf_k, tf_o).a);
+                ++evaluated;
+            }, []() {});
+            all = s == 0 ? S : all * S;
         }
-        f.shade[q] = f.step == 0 ? S : f.shade[q] * S;
+        f.shade[slot0 + i] = all;
     }
     count_held(f.samples, evaluated);
 }
@@ -412,17 +693,12 @@ __global__ __launch_bounds__(256) void tet_resolve(TetFrameParams f) {
 
 template <int kLocator>
 void launch_tet_stages(TetFrameParams p, int stages, hipStream_t stream) {
-    const dim3 tiles(p.total_tiles), threads(kTetThreads);
+    const dim3 tiles(p.total_tiles), one(64), threads(64 * kWaves);
     if (p.total_tiles <= 0) return;
-    if (stages & kTetCount) hipLaunchKernelGGL((tet_march<kTetCount, kLocator>), tiles, threads, 0, stream, p);
-    if (stages & kTetRecord) hipLaunchKernelGGL((tet_march<kTetRecord, kLocator>), tiles, threads, 0, stream, p);
-    if ((stages & kTetShadow) && p.total > 0) {
-        const unsigned grid = (unsigned)min((p.total + 255) / 256, (long long)65536);
-        for (int s = 0; s < p.n; ++s) {
-            p.step = s;
-            hipLaunchKernelGGL(tet_shadow_step<kLocator>, dim3(grid), dim3(256), 0, stream, p);
-        }
-    }
+    if (stages & kTetCount) hipLaunchKernelGGL((tet_march<kTetCount, kLocator>), tiles, one, 0, stream, p);
+    if (stages & kTetRecord) hipLaunchKernelGGL((tet_march<kTetRecord, kLocator>), tiles, one, 0, stream, p);
+    if ((stages & kTetShadow) && p.total > 0)
+        hipLaunchKernelGGL(tet_shadow<kLocator>, dim3(p.total_tiles, kShadowSplit / 4), dim3(256), 0, stream, p);
     if (stages & kTetMarch) hipLaunchKernelGGL((tet_march<kTetMarch, kLocator>), tiles, threads, 0, stream, p);
     if (stages & kTetShaded) hipLaunchKernelGGL((tet_march<kTetShaded, kLocator>), tiles, threads, 0, stream, p);
 }
@@ -438,6 +714,12 @@ hipError_t launch_tet_values(const float* vertex_values, int32_t n_input, const 
 }
 
 hipError_t launch_tet_frame(TetFrameParams p, int stages, hipStream_t stream) {
+    if (stages == kTetAffine) {
+        if (p.one.n_tets > 0)
+            hipLaunchKernelGGL(tet_affine, dim3((p.one.n_tets + 255) / 256), dim3(256), 0, stream, p.one,
+                               reinterpret_cast<double2_t*>(const_cast<double*>(p.one.affine)));
+        return hipGetLastError();
+    }
     if (p.locator == kTetBvh)
         launch_tet_stages<kTetBvh>(p, stages, stream);
     else
