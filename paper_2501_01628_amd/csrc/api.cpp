@@ -1689,7 +1689,10 @@ vr_status vr_render_rqc(vr_context ctx, int32_t n, const vr_brick* bricks, const
     p.tf = ctx->tf;
     p.dt = ctx->dt;
     p.inv_dt = 1.0 / ctx->dt;
-    for (int c = 0; c < 3; ++c) p.light[c] = light->direction[c] / ln;
+    for (int c = 0; c < 3; ++c) {
+        p.light[c] = light->direction[c] / ln;
+        p.inv_light[c] = 1.0 / p.light[c];
+    }
     p.ert_eps = ctx->ert_eps;
     p.ambient = light->ambient;
     p.shadows = shadows ? 1 : 0;
@@ -1701,6 +1704,7 @@ vr_status vr_render_rqc(vr_context ctx, int32_t n, const vr_brick* bricks, const
     p.kf = reinterpret_cast<int32_t*>(ws + off[1]);
     p.offsets = reinterpret_cast<long long*>(ws + off[2]);
     p.total = pl.total;
+    for (const RqcBrick& r : tab) p.tiles += (r.roi_w + 7) / 8 * ((r.roi_h + 7) / 8);
     p.shade = shade;
     p.segs = reinterpret_cast<float*>(ws + off[4]);
     p.out = out;

@@ -212,11 +212,12 @@ struct RqcParams {
     TFK tf;
     double dt, inv_dt;
     double light[3];            // unit direction toward the light
+    double inv_light[3];        // 1 / light
     float ert_eps;
     float ambient;              // a0: emission scaled by a0 + (1 - a0) S
     int32_t shadows;            // 0: a0 = 1, no shadow rays traced
     int32_t n;                  // bricks (ranks)
-    int32_t step;               // cycle step of a step launch
+    int32_t tiles;              // 8 x 8 pixel tiles of all bricks' ROIs
     int32_t width, height;
     const RqcBrick* bricks;     // device, n
     long long n_entries;        // sum of ROI pixels over the bricks

@@ -122,14 +122,13 @@ __device__ inline bool setup_ray(const CameraK& cam, const BrickK& b, double dt,
     return true;
 }
 
-// Any ray (origin o, unit direction d, float64) and its owned run [kf, kl] of
-// the lattice t_k = (k + 1/2) dt in brick b, by the ownership scan of
-// setup_ray (shadow rays start at a primary sample and head for the light).
-__device__ inline bool setup_ray_from(double o0, double o1, double o2, double d0, double d1, double d2,
-                                      const BrickK& b, double dt, RaySetup& rs) {
+// The owned run [kf, kl] of any ray (rs.o, unit rs.d, float64) on the lattice
+// t_k = (k + 1/2) dt in brick b, by the ownership scan of setup_ray (shadow
+// rays start at a primary sample and head for the light).  inv_d = 1 / rs.d
+// and inv_dt: the box's parameters need no more than the scan's margin of two
+// samples, so products stand in for setup_ray's quotients.
+__device__ inline bool owned_run(RaySetup& rs, const BrickK& b, double dt, double inv_dt, const double (&inv_d)[3]) {
 #pragma clang fp contract(off)
-    rs.o[0] = o0; rs.o[1] = o1; rs.o[2] = o2;
-    rs.d[0] = d0; rs.d[1] = d1; rs.d[2] = d2;
     double tin = 0.0, tout = INFINITY;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -137,13 +136,13 @@ __device__ inline bool setup_ray_from(double o0, double o1, double o2, double d0
             if (rs.o[c] < b.lo[c] || rs.o[c] >= b.hi[c]) return false;
             continue;
         }
-        double ta = (b.lo[c] - rs.o[c]) / rs.d[c], tb = (b.hi[c] - rs.o[c]) / rs.d[c];
+        const double ta = (b.lo[c] - rs.o[c]) * inv_d[c], tb = (b.hi[c] - rs.o[c]) * inv_d[c];
         tin = fmax(tin, fmin(ta, tb));
         tout = fmin(tout, fmax(ta, tb));
     }
     if (!(tout >= tin - 2.0 * dt)) return false;
-    long long k0 = (long long)fmax(floor(tin / dt - 0.5) - 2.0, 0.0);
-    long long k1 = (long long)(ceil(tout / dt - 0.5) + 2.0);
+    const long long k0 = (long long)fmax(floor(tin * inv_dt - 0.5) - 2.0, 0.0);
+    const long long k1 = (long long)(ceil(tout * inv_dt - 0.5) + 2.0);
     if (k1 < k0) return false;
     long long kf = k0;
     while (kf <= k1 && !owned(rs.o, rs.d, ((double)kf + 0.5) * dt, b.lo, b.hi)) ++kf;
@@ -325,6 +324,104 @@ __device__ inline float trilinear(const TS* __restrict__ vox, const Cell& c, int
 // Row pitch of the stored brick (elements): x extent rounded up to 8, so that
 // every row starts 16-byte aligned for both storage precisions.
 __host__ __device__ inline int row_pitch(int snx) { return (snx + 7) & ~7; }
+
+// Corner reads straight from the brick by 32-bit byte offsets: the four rows
+// of a cell (y, y + 1 on z, z + 1) are four uniform bases with one per-lane
+// offset, and both x corners of a row one load (4 vector loads and 4 integer
+// instructions a sample; 8 corner addresses of 64 bits each took 8 loads, or
+// 4 once merged, and about 25).  For bricks below 4 GiB whose slices are below
+// 8 MiB (the offset products are 24-bit); the others use trilinear().
+template <typename TS>
+struct Rows {
+    const char* base;
+    unsigned dy, dz;     // bytes to the next row and slice
+    unsigned last;       // largest offset whose eight corners lie in the brick
+};
+
+__device__ inline bool fits_rows(const BrickK& b, int elem_bytes) {
+    const long long slice = (long long)row_pitch(b.sdim[0]) * b.sdim[1] * elem_bytes;
+    return slice < (1LL << 23) && slice * b.sdim[2] < (1LL << 32);
+}
+
+template <typename TS>
+__device__ inline Rows<TS> make_rows(const BrickK& b) {
+    Rows<TS> r;
+    r.base = reinterpret_cast<const char*>(b.data);
+    r.dy = (unsigned)(row_pitch(b.sdim[0]) * sizeof(TS));
+    r.dz = r.dy * (unsigned)b.sdim[1];
+    r.last = r.dz * (unsigned)(b.sdim[2] - 1) - r.dz + r.dy * (unsigned)(b.sdim[1] - 2) +
+             (unsigned)((b.sdim[0] - 2) * sizeof(TS));
+    return r;
+}
+
+// Offset of the anchor's voxel (the fraction's floor added per sample), modulo 2^32.
+template <typename TS>
+__device__ inline unsigned anchor_offset(const Rows<TS>& r, const Anchor& a) {
+    return (unsigned)a.ia2 * r.dz + (unsigned)a.ia1 * r.dy + (unsigned)a.ia0 * (unsigned)sizeof(TS);
+}
+
+// Fractions and corner offset of sample j after the anchor: locate()'s
+// position.  For owned samples the clamp never acts; it keeps the reads of
+// samples past a run's end inside the brick.
+struct Spot {
+    float fx, fy, fz;
+    unsigned off;
+};
+
+template <typename TS>
+__device__ inline Spot locate_rows(const Rows<TS>& r, unsigned anchor, const Anchor& a, const Step& st, float fj) {
+    const float x = fmaf(fj, st.s0, a.uf0), y = fmaf(fj, st.s1, a.uf1), z = fmaf(fj, st.s2, a.uf2);
+    Spot s;
+    s.fx = fract(x); s.fy = fract(y); s.fz = fract(z);
+    const unsigned off = anchor + (unsigned)__mul24(floor_int(z), (int)r.dz) +
+                         (unsigned)__mul24(floor_int(y), (int)r.dy) + (unsigned)floor_int(x) * (unsigned)sizeof(TS);
+    s.off = min(off, r.last);
+    return s;
+}
+
+// A row's two x corners as loaded, and the interpolation (lerp3's order).
+template <typename TS>
+struct PairOf;
+template <>
+struct PairOf<float> {
+    typedef float type __attribute__((ext_vector_type(2)));
+    typedef type unaligned __attribute__((aligned(4)));
+    __device__ static float lo(type v) { return v.x; }
+    __device__ static float hi(type v) { return v.y; }
+};
+template <>
+struct PairOf<__half> {
+    typedef unsigned type;
+    typedef type unaligned __attribute__((aligned(2)));
+    __device__ static float lo(type v) { return __half2float(__ushort_as_half((unsigned short)v)); }
+    __device__ static float hi(type v) { return __half2float(__ushort_as_half((unsigned short)(v >> 16))); }
+};
+template <typename TS>
+struct Corners {
+    typename PairOf<TS>::type r00, r10, r01, r11;    // (y, z), (y + 1, z), (y, z + 1), (y + 1, z + 1)
+};
+
+template <typename TS>
+__device__ inline Corners<TS> gather_rows(const Rows<TS>& r, unsigned off) {
+    typedef __attribute__((address_space(1))) const char gchar;
+    typedef __attribute__((address_space(1))) const typename PairOf<TS>::unaligned gpair;
+    gchar* b = (gchar*)r.base;
+    Corners<TS> c;
+    c.r00 = *(gpair*)(b + off);
+    c.r10 = *(gpair*)(b + r.dy + off);
+    c.r01 = *(gpair*)(b + r.dz + off);
+    c.r11 = *(gpair*)(b + (r.dz + r.dy) + off);
+    return c;
+}
+
+template <typename TS>
+__device__ inline float lerp_rows(const Spot& s, const Corners<TS>& c) {
+    typedef PairOf<TS> P;
+    Cell q{};
+    q.fx = s.fx; q.fy = s.fy; q.fz = s.fz;
+    return lerp3(q, P::lo(c.r00), P::hi(c.r00), P::lo(c.r10), P::hi(c.r10), P::lo(c.r01), P::hi(c.r01),
+                 P::lo(c.r11), P::hi(c.r11));
+}
 
 // Classification table in LDS: entry i = (r, g, b, a') with a' = alpha *
 // opacity_scale * dt * log2(e), and the difference to entry i + 1.
