@@ -43,19 +43,13 @@ struct LaneState {
 // wherever the runs of a ray are cut, so every path stops a ray at the same
 // sample; a ray may take one sample past T < eps, which changes its colour by
 // less than eps.
-template <bool kCkpt, typename Sample>
-__device__ inline bool march_run(const MarchParams& p, const TFTable& tft, const RaySetup& rs,
-                                 long long kb, int j0, int j1, long long pix, float tf_k,
+template <typename Sample>
+__device__ inline bool march_run(const TFTable& tft, const RaySetup& rs, long long kb, int j0, int j1, float tf_k,
                                  float tf_o, float eps, LaneState& s, Sample sample) {
-    auto accumulate = [&](const Classified& e, int j) {
+    auto accumulate = [&](const Classified& e) {
         // no contraction (T - T x must not become an FMA in some
         // instantiations only: every path rounds alike)
 #pragma clang fp contract(off)
-        if (kCkpt) {
-            const long long q = kb + j - rs.kf;
-            if (q % p.ckpt_interval == 0 && q / p.ckpt_interval < p.ckpt_nseg)
-                p.ckpt[pix * p.ckpt_nseg + q / p.ckpt_interval] = s.T;
-        }
         // emission-absorption: T_next = T exp2(-a'), weight = T - T_next
         const float Tn = s.T * trans_exp2(-e.a);
         const float w = s.T - Tn;
@@ -67,7 +61,7 @@ __device__ inline bool march_run(const MarchParams& p, const TFTable& tft, const
     int j = j0;
     float fj = (float)j0;
     if (((kb + j0 - rs.kf) & 1) && j < j1) {   // second sample of a pair begun in the previous run
-        accumulate(classify(tft, sample(fj), tf_k, tf_o), j);
+        accumulate(classify(tft, sample(fj), tf_k, tf_o));
         ++j;
         fj += 1.0f;
         if (s.T < eps) {
@@ -81,8 +75,8 @@ __device__ inline bool march_run(const MarchParams& p, const TFTable& tft, const
         const float v1 = sample(fj + 1.0f);
         const Classified e0 = classify(tft, v0, tf_k, tf_o);
         const Classified e1 = classify(tft, v1, tf_k, tf_o);
-        accumulate(e0, j);
-        accumulate(e1, j + 1);
+        accumulate(e0);
+        accumulate(e1);
         if (s.T < eps) {
             s.evaluated += j - j0 + 2;
             s.stopped = true;
@@ -90,7 +84,7 @@ __device__ inline bool march_run(const MarchParams& p, const TFTable& tft, const
         }
     }
     // first sample of a pair: its test comes after the next sample (next run)
-    if (j < j1) accumulate(classify(tft, sample(fj), tf_k, tf_o), j);
+    if (j < j1) accumulate(classify(tft, sample(fj), tf_k, tf_o));
     s.evaluated += j1 - j0;
     return true;
 }
@@ -107,12 +101,17 @@ __device__ inline bool march_run(const MarchParams& p, const TFTable& tft, const
 // wavefront would otherwise take whenever any of its rays needs one.  The
 // arithmetic of every sample, the order of accumulation and the termination
 // tests are those of march_run, so results are bit-identical.
-template <typename Pre, typename Gather, typename Value>
+// before(): called in front of every sample accumulated.  kAhead: the voxel
+// reads of the next pair are issued before this pair's values are used (reads
+// from HBM, which few wavefronts do not hide; the pair past the run's end is
+// read from clamped addresses and dropped).
+template <bool kAhead, typename Pre, typename Gather, typename Value, typename Before>
 __device__ inline bool march_run_pipe(const TFTable& tft, const RaySetup& rs, long long kb, int j0,
                                       int j1, float tf_k, float tf_o, float eps, LaneState& s,
-                                      Pre pre, Gather gather, Value value) {
+                                      Pre pre, Gather gather, Value value, Before before) {
     auto accumulate = [&](const Classified& e) {
 #pragma clang fp contract(off)
+        before();
         const float Tn = s.T * trans_exp2(-e.a);
         const float w = s.T - Tn;
         s.C0 = fmaf(w, e.r, s.C0);
@@ -122,13 +121,28 @@ __device__ inline bool march_run_pipe(const TFTable& tft, const RaySetup& rs, lo
     };
     if (j0 >= j1) return true;
     // first sample of the pair that holds sample j0
-    for (int j = j0 - (int)((kb + j0 - rs.kf) & 1); j < j1; j += 2) {
+    int j = j0 - (int)((kb + j0 - rs.kf) & 1);
+    using G = decltype(gather(pre(0.0f)));
+    G na, nb;
+    if constexpr (kAhead) {
+        na = gather(pre((float)j));
+        nb = gather(pre((float)j + 1.0f));
+    }
+    for (; j < j1; j += 2) {
         const float fj = (float)j;
-        const auto pa = pre(fj);
-        const auto pb = pre(fj + 1.0f);
-        __builtin_amdgcn_sched_barrier(0);
-        const auto ga = gather(pa);
-        const auto gb = gather(pb);
+        G ga, gb;
+        if constexpr (kAhead) {
+            ga = na;
+            gb = nb;
+            na = gather(pre(fj + 2.0f));
+            nb = gather(pre(fj + 3.0f));
+        } else {
+            const auto pa = pre(fj);
+            const auto pb = pre(fj + 1.0f);
+            __builtin_amdgcn_sched_barrier(0);
+            ga = gather(pa);
+            gb = gather(pb);
+        }
         __builtin_amdgcn_sched_barrier(0);
         const float v0 = value(ga), v1 = value(gb);
         // classification in two stages (table index, then both table reads)
@@ -249,35 +263,76 @@ __device__ inline bool march_run_deep(const TFTable& tft, const RaySetup& rs, lo
     return true;
 }
 
-// Whole ray from HBM, block by block.
-template <typename TS, bool kCkpt>
-__device__ inline void march_ray_direct(const MarchParams& p, const TFTable& tft,
-                                        const RaySetup& rs, long long pix, float tf_k, float tf_o,
-                                        float eps, LaneState& s) {
-    const BrickK& b = p.brick;
-    const TS* __restrict__ vox = reinterpret_cast<const TS*>(b.data);
-    const int snx = b.sdim[0], sny = b.sdim[1], snz = b.sdim[2];
-    const int pitch = row_pitch(snx);
-    const long long sxy = (long long)pitch * sny;
-    const Step st = make_step(rs, b, p.dt);
-    const Blocks bl = make_blocks(rs, b);
+// Whole ray from HBM, block by block, with the checkpoints of the
+// transmittance in front of every ckpt_interval-th sample (kCkpt; counted
+// down: the interval is a run-time number, and a 64-bit remainder a sample
+// cost more than its reads).  Bound by the vector memory unit: four row reads a
+// sample, two pairs in flight.  Checkpointed forward of 128^3 at 512x512, step
+// 0.5: 187 us a view before (8 corner addresses of 64 bits, a remainder and
+// one pair in flight per sample), 139 by rows; the second pair took another
+// 30 us off each view (8 views, forward and backward: 5.03 to 4.79 ms).  16
+// float16 bricks of 512 x 256 x 256, 384x384 crop, step 0.25: 896 to 630 us.
+template <typename TS, bool kCkpt, typename Blk>
+__device__ inline void march_ray_blocks(const MarchParams& p, const TFTable& tft, const RaySetup& rs, long long pix,
+                                        float tf_k, float tf_o, float eps, LaneState& s, Blk blk) {
+    const Step st = make_step(rs, p.brick, p.dt);
+    const Blocks bl = make_blocks(rs, p.brick);
+    int left = 0, seg = 0;              // samples to the next checkpoint, and its number
+    auto before = [&]() {
+        if constexpr (kCkpt) {
+            if (left == 0) {
+                if (seg < p.ckpt_nseg) p.ckpt[pix * p.ckpt_nseg + seg] = s.T;
+                ++seg;
+                left = p.ckpt_interval;
+            }
+            --left;
+        }
+    };
     long long n = block_of(bl, p.dt, p.inv_dt, rs.kf);
     long long k = rs.kf;
     while (k <= rs.kl) {
         const long long knext = block_start(bl, p.inv_dt, n + 1);
         const long long kend = min(knext - 1, rs.kl);
         if (kend >= k) {
-            const Anchor an = make_anchor(rs, b, p.dt, k);
-            auto sample = [&](float fj) {
-                return trilinear(vox, locate(an, st, fj, snx, sny, snz), pitch, sxy);
-            };
-            if (!march_run<kCkpt>(p, tft, rs, k, 0, (int)(kend - k + 1), pix, tf_k, tf_o, eps, s,
-                                  sample))
-                return;
+            if (!blk(make_anchor(rs, p.brick, p.dt, k), st, k, (int)(kend - k + 1), before)) return;
             k = kend + 1;
         }
         ++n;
     }
+}
+
+template <typename TS, bool kCkpt>
+__device__ inline void march_ray_direct(const MarchParams& p, const TFTable& tft,
+                                        const RaySetup& rs, long long pix, float tf_k, float tf_o,
+                                        float eps, LaneState& s) {
+    const BrickK& b = p.brick;
+    if (fits_rows(b, sizeof(TS))) {
+        const Rows<TS> rows = make_rows<TS>(b);
+        struct Read {
+            Spot s;
+            Corners<TS> c;
+        };
+        march_ray_blocks<TS, kCkpt>(p, tft, rs, pix, tf_k, tf_o, eps, s,
+                                    [&](const Anchor& an, const Step& st, long long k, int n, auto before) {
+            const unsigned base = anchor_offset(rows, an);
+            return march_run_pipe<true>(tft, rs, k, 0, n, tf_k, tf_o, eps, s,
+                                  [&](float fj) { return locate_rows(rows, base, an, st, fj); },
+                                  [&](const Spot& q) { return Read{q, gather_rows(rows, q.off)}; },
+                                  [&](const Read& r) { return lerp_rows(r.s, r.c); }, before);
+        });
+        return;
+    }
+    const TS* __restrict__ vox = reinterpret_cast<const TS*>(b.data);
+    const int snx = b.sdim[0], sny = b.sdim[1], snz = b.sdim[2];
+    const int pitch = row_pitch(snx);
+    const long long sxy = (long long)pitch * sny;
+    march_ray_blocks<TS, kCkpt>(p, tft, rs, pix, tf_k, tf_o, eps, s,
+                                [&](const Anchor& an, const Step& st, long long k, int n, auto before) {
+        return march_run_pipe<false>(tft, rs, k, 0, n, tf_k, tf_o, eps, s,
+                              [&](float fj) { return locate(an, st, fj, snx, sny, snz); },
+                              [&](const Cell& c) { return trilinear(vox, c, pitch, sxy); },
+                              [&](float v) { return v; }, before);
+    });
 }
 
 __device__ inline void finish(const MarchParams& p, bool valid, long long pix, float depth,
@@ -680,13 +735,12 @@ __device__ void slab_walk(const MarchParams& p, StagedShared& sh, int& buf, cons
                         // staged loop, whose scheduling barriers the slab's lock-step
                         // waves cannot hide)
                         auto sample_lds = [&](float fj) { return value(gather(pre(fj))); };
-                        cont = march_run<false>(p, tft, rs, k_cur, j0, j1, pix, tf_k, tf_o, eps, s, sample_lds);
+                        cont = march_run(tft, rs, k_cur, j0, j1, tf_k, tf_o, eps, s, sample_lds);
                     } else {
                         auto sample_hbm = [&](float fj) {
                             return trilinear(vox, locate(an, st, fj, snx, sny, snz), pitch, sxy);
                         };
-                        cont = march_run<false>(p, tft, rs, k_cur, j0, j1, pix, tf_k, tf_o, eps, s,
-                                                sample_hbm);
+                        cont = march_run(tft, rs, k_cur, j0, j1, tf_k, tf_o, eps, s, sample_hbm);
                     }
                     kpos = ke;
                 }
@@ -1320,8 +1374,8 @@ __device__ void ring_consume(const MarchParams& p, RingShared<NCW>& sh, const Ri
                     cont = march_run_deep(tft, rs, k_anchor, (int)(k_cur - k_anchor), (int)(ke - k_anchor),
                                           tf_k, tf_o, eps, s, pre, gather, value);
                 else
-                    cont = march_run_pipe(tft, rs, k_anchor, (int)(k_cur - k_anchor), (int)(ke - k_anchor),
-                                          tf_k, tf_o, eps, s, pre, gather, value);
+                    cont = march_run_pipe<false>(tft, rs, k_anchor, (int)(k_cur - k_anchor), (int)(ke - k_anchor),
+                                          tf_k, tf_o, eps, s, pre, gather, value, []() {});
                 k_cur = ke;
                 alive = cont && k_cur <= rs.kl;
             }
