@@ -447,7 +447,8 @@ vr_status vr_batch_release(vr_batch batch);
  * transfer-function and inverse-volume fitting.  The forward pass stores the
  * transmittance in front of every `interval`-th owned sample of every ray
  * (segment checkpoints, 1 <= interval <= DPVR_MAX_CKPT_INTERVAL); the
- * backward re-marches each segment from its checkpoint, last segment first.
+ * backward takes them as a record of that forward pass (their size is
+ * checked) and marches every ray again, in stretches of its own.
  * Early termination is off in both passes.  Gradients are exact derivatives
  * of the rendered image (readings: emission-absorption as above; the table
  * lookup is differentiated on the segment it uses, min(floor(s), 254), and
