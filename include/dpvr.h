@@ -221,7 +221,11 @@ vr_status vr_set_render_params(vr_context ctx, double dt, float ert_epsilon);
 /* Launch path of the forward march; every path computes bit-identical
  * images (the sample positions and values do not depend on it):
  *   VR_PATH_STAGED  a workgroup per 16x16 pixel tile stages each slab of
- *                   brick slices its rays cross through LDS (default);
+ *                   brick slices its rays cross through LDS (default;
+ *                   vr_render_partials takes the direct march instead for
+ *                   bricks of a storage precision whose vr_set_march_config
+ *                   was not called, where that is the faster one: few tiles,
+ *                   or float32 bricks seen at few voxels a pixel);
  *   VR_PATH_DIRECT  every lane reads its voxels from HBM (vr_render_partials:
  *                   the same persistent work queue; vr_render_partial: one
  *                   wavefront per 8x8 tile). */

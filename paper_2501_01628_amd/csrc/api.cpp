@@ -41,6 +41,7 @@ struct vr_context_s {
     // fastest measured on the 1920x1080 frame of 16 bricks -- float32: ring,
     // 32-pixel tiles, 4-slice chunks; float16: slab
     MarchCfg cfg[2] = {{kStagingRing, 32, 4}, {kStagingSlab, 16, 4}};
+    bool cfg_chosen[2] = {false, false};   // set by vr_set_march_config
     hipStream_t stream = nullptr;
     bool has_camera = false, has_tf = false;
     CameraK cam{};
@@ -66,6 +67,7 @@ struct vr_context_s {
     // that many partials allocates nothing)
     std::vector<MarchParams> fjobs;
     std::vector<int32_t> fprefix;
+    bool fdirect[2] = {false, false};      // the current frame's groups that march from HBM
     // the last vr_rqc_plan: its workspace, bricks, camera and spacing, plan
     // entries and owned primary samples (vr_render_rqc must match it)
     struct {
@@ -545,6 +547,7 @@ vr_status vr_set_march_config(vr_context ctx, vr_dtype storage, vr_staging stagi
         return fail(ctx, VR_ERR_INVALID_ARG, "vr_set_march_config: slab staging takes 16-pixel tiles, ring staging "
                     "16 or 32 with chunks of 4 or 8 slices (got %d, %d, %d)", (int)staging, tile_width, chunk_slices);
     ctx->cfg[storage == VR_F16 ? 1 : 0] = MarchCfg{st, tile_width, st == kStagingSlab ? 4 : chunk_slices};
+    ctx->cfg_chosen[storage == VR_F16 ? 1 : 0] = true;
     return ok(ctx);
 }
 
@@ -720,10 +723,50 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
     return n;
 }
 
-// Tile width of the frame queue of storage group g (0 float32, 1 float16)
-// with the context's current path.
-static int frame_tile_w(vr_context ctx, int g) {
-    return ctx->path == kPathDirect || ctx->cfg[g].staging == kStagingSlab ? 16 : ctx->cfg[g].tile_w;
+// Whether the frame queue of storage group g (0 float32, 1 float16) marches
+// from HBM, with the context's current path: every path gives the same bits.
+// Staging pays by the samples that a staged voxel serves and needs a
+// workgroup's LDS for each tile, so the direct march is the faster one
+// * when the tiles are few (2 per CU; 1.4 for float16 below half a voxel a
+//   step): a staged workgroup then walks the slabs of one tile alone, and the
+//   frame lasts as long as one
+//   (step 0.5, staged and direct: 64^3 at 283x212, 210 tiles, 98 and 68 us,
+//   float16 76 and 64; 160^3 at 353x265, 388 tiles, 203 and 155, float16 188
+//   and 172; 320^3 at 353x265, 503 tiles, 491 and 395, float16 504 and 300;
+//   160^3 at 441x331, 608 tiles, 190 and 183, float16 178 and 195; step 0.25,
+//   160^3 float16 at 415x311, 505 tiles, 277 and 292);
+// * for float32 bricks seen at few voxels a pixel, where the lanes of a
+//   wavefront share the lines they read, up to sqrt(1.28 step) voxels a pixel
+//   with the step in voxels: a coarse step has fewer samples per staged voxel
+//   (step 0.5, line at 0.8: 512^3 at 0.5 voxels a pixel 4.05 ms staged and 3.13
+//   direct, at 0.8 0.98 to 1.17 times as fast, at 1.0 1.26 ms and 1.40; step
+//   0.25, line at 0.57, 320^3: at 0.5 1.93 and 1.76, at 0.75 1.01 and 1.05;
+//   step 1, line at 1.13: at 1.0 339 us and 302, at 1.4 315 and 335).  float16
+//   bricks stage twice the voxels in the same LDS: direct is 0.64 to 1.04 times
+//   as fast there.
+// A staged configuration that the caller chose is taken as it is.
+static bool frame_direct(vr_context ctx, int g, const MarchParams* jobs, int n) {
+    if (ctx->path == kPathDirect) return true;
+    if (ctx->cfg_chosen[g]) return false;
+    // voxels a pixel at a brick's centre, over the line: weighted by its tiles
+    double tiles = 0.0, pixel = 0.0;
+    bool few = g == 0;                  // two tiles per CU are few
+    for (int i = 0; i < n; ++i) {
+        const CameraK& c = jobs[i].cam;
+        const BrickK& b = jobs[i].brick;
+        const double t = queue_tiles(jobs[i].roi_w, jobs[i].roi_h, 16);
+        double depth = 1.0;
+        if (c.kind == 0) {
+            depth = 0.0;
+            for (int k = 0; k < 3; ++k) depth += (0.5 * (b.lo[k] + b.hi[k]) - c.eye[k]) * c.f[k];
+        }
+        const double fine = std::min(b.spacing[0], std::min(b.spacing[1], b.spacing[2]));
+        tiles += t;
+        few = few || 2.0 * jobs[i].dt >= fine;
+        const double vpp = std::fabs(depth) * 2.0 * c.ay / ((double)c.height * fine);
+        pixel += t * vpp / std::sqrt(1.28 * jobs[i].dt / fine);
+    }
+    return tiles <= (few ? 2.0 : 1.4) * ctx->cus || (g == 0 && pixel <= tiles);
 }
 
 // Job table and tile prefix of a frame of n partials, grouped by storage
@@ -742,9 +785,8 @@ static vr_status frame_tables(vr_context ctx, int32_t n, const vr_brick* bricks,
     }
     int n32 = 0;
     for (int pass = 0; pass < 2; ++pass) {
-        int32_t acc = 0;
         const int base = pass == 0 ? 0 : n32 + 1;   // prefix offset of this group
-        int cnt = 0;
+        const int job0 = (int)jobs.size();
         for (int i = 0; i < n; ++i) {
             if (!live(bricks[i]) || bricks[i]->ctx != ctx)
                 return fail(ctx, VR_ERR_INVALID_HANDLE, "%s: invalid brick %d", who, i);
@@ -752,10 +794,15 @@ static vr_status frame_tables(vr_context ctx, int32_t n, const vr_brick* bricks,
             MarchParams p;
             vr_status st = prepare_march(ctx, bricks[i], &parts[i], who, p);
             if (st != VR_OK) return st;
-            prefix[base + cnt] = acc;
-            acc += queue_tiles(parts[i].w, parts[i].h, frame_tile_w(ctx, pass));
             jobs.push_back(p);
-            ++cnt;
+        }
+        const int cnt = (int)jobs.size() - job0;
+        ctx->fdirect[pass] = frame_direct(ctx, pass, jobs.data() + job0, cnt);
+        const int tile_w = ctx->fdirect[pass] ? 16 : ctx->cfg[pass].tile_w;
+        int32_t acc = 0;
+        for (int j = 0; j < cnt; ++j) {
+            prefix[base + j] = acc;
+            acc += queue_tiles(jobs[job0 + j].roi_w, jobs[job0 + j].roi_h, tile_w);
         }
         prefix[base + cnt] = acc;
         if (pass == 0) n32 = cnt;
@@ -797,15 +844,16 @@ static hipError_t launch_frame(vr_context ctx, char* ws, size_t off_t, size_t of
     const MarchParams* djobs = reinterpret_cast<const MarchParams*>(ws + off_j);
     const int32_t* dtiles = reinterpret_cast<const int32_t*>(ws + off_t);
     int32_t* heads = reinterpret_cast<int32_t*>(ws);
-    const int staged = ctx->path == kPathDirect ? 0 : 1;
     hipError_t e = hipSuccess;
     if (n32 > 0) {
-        const int tw = frame_tile_w(ctx, 0), ch = ctx->cfg[0].chunk, sk = ctx->cfg[0].staging;
+        const int staged = ctx->fdirect[0] ? 0 : 1, tw = staged ? ctx->cfg[0].tile_w : 16, ch = ctx->cfg[0].chunk,
+                  sk = ctx->cfg[0].staging;
         QueueParams q{djobs, dtiles, n32, prefix[n32], heads, staged, sk, tw, ch, err_word(ctx)};
         e = launch_march_queue(q, kF32, queue_workgroups(ctx, kF32, staged, sk, tw, ch), ctx->stream);
     }
     if (e == hipSuccess && n - n32 > 0) {
-        const int tw = frame_tile_w(ctx, 1), ch = ctx->cfg[1].chunk, sk = ctx->cfg[1].staging;
+        const int staged = ctx->fdirect[1] ? 0 : 1, tw = staged ? ctx->cfg[1].tile_w : 16, ch = ctx->cfg[1].chunk,
+                  sk = ctx->cfg[1].staging;
         QueueParams q{djobs + n32, dtiles + n32 + 1, n - n32, prefix[n + 1], heads + kQueueParts, staged, sk, tw,
                       ch, err_word(ctx)};
         e = launch_march_queue(q, kF16, queue_workgroups(ctx, kF16, staged, sk, tw, ch), ctx->stream);

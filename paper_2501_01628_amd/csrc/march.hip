@@ -1487,14 +1487,23 @@ __global__ __launch_bounds__((NCW + 1) * 64, 2) void march_staged(MarchParams p)
 }
 
 // One 16x16 tile, every lane marching its own ray from HBM (no staging, no
-// workgroup-wide steps).
+// workgroup-wide steps).  Bound by the vector memory unit, which takes a
+// wavefront's loads by the lines they touch, cheapest when lanes next to each
+// other share one: lanes run along the rows of an 8x8 quarter, whose rays lie
+// next to each other in x and share rows of voxels, unless the camera looks
+// along x, where four pixels in a square share a row best (641x479 frame of
+// 211 x 149 x 173 at azimuth 100 degrees: 260 us in rows, 221 in squares; from
+// 30 degrees, 1024 x 1024 x 512 at 1920x1080: 3.66 ms in rows, 3.80).
 template <typename TS>
 __device__ void direct_tile(const MarchParams& p, int tile, const TFTable& tft) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tiles_x16 = (p.roi_w + 15) / 16;
     const int tx = tile % tiles_x16, ty = tile / tiles_x16;
-    const int lx = tx * 16 + (wave & 1) * 8 + (lane & 7);
-    const int ly = ty * 16 + (wave >> 1) * 8 + (lane >> 3);
+    const bool quads = fabs(p.cam.f[0]) > fmax(fabs(p.cam.f[1]), fabs(p.cam.f[2]));
+    const int col = quads ? (lane & 1) | (lane >> 1 & 2) | (lane >> 2 & 4) : lane & 7;
+    const int row = quads ? (lane >> 1 & 1) | (lane >> 2 & 2) | (lane >> 3 & 4) : lane >> 3;
+    const int lx = tx * 16 + (wave & 1) * 8 + col;
+    const int ly = ty * 16 + (wave >> 1) * 8 + row;
     const bool valid = lx < p.roi_w && ly < p.roi_h;
     const long long pix = (long long)ly * p.roi_w + lx;
     const float tf_k = 255.0f / (p.tf.vmax - p.tf.vmin);
