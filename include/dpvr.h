@@ -225,7 +225,8 @@ vr_status vr_set_render_params(vr_context ctx, double dt, float ert_epsilon);
  *                   vr_render_partials takes the direct march instead for
  *                   bricks of a storage precision whose vr_set_march_config
  *                   was not called, where that is the faster one: few tiles,
- *                   or float32 bricks seen at few voxels a pixel);
+ *                   small bricks, or float32 bricks seen at few voxels a
+ *                   pixel);
  *   VR_PATH_DIRECT  every lane reads its voxels from HBM (vr_render_partials:
  *                   the same persistent work queue; vr_render_partial: one
  *                   wavefront per 8x8 tile). */
@@ -397,7 +398,8 @@ vr_status vr_batch_launch(vr_batch batch);
  * length (ring: 4 or 8 slices, i.e. the samples a marching wavefront takes
  * between synchronisations) x job order (as given, or grouped by brick so
  * that the cameras of one brick run together and share L2) x persistent
- * workgroups per CU -- over `reps` replays, keep the
+ * workgroups per CU, and the direct march where a new batch would take it --
+ * over `reps` replays, keep the
  * fastest and report its average time per launch in *best_ms.  When the
  * environment variable DPVR_AUTOTUNE_CACHE names a file, a configuration
  * found earlier for the same batch shape and device is reused from it (and
@@ -407,7 +409,9 @@ vr_status vr_batch_autotune(vr_batch batch, int32_t reps, double* best_ms);
 /* The batch's current configuration: workgroups per CU, job order
  * (0 = as given, 1 = grouped by brick), staged family (vr_staging), tile
  * width and chunk length.  Any pointer may be NULL.  A new batch starts with
- * the context's march configuration and the most workgroups per CU that fit. */
+ * the context's march configuration and the most workgroups per CU that fit;
+ * the bricks of a storage precision whose vr_set_march_config was not called
+ * are marched directly (VR_PATH_DIRECT) where that is the faster one. */
 vr_status vr_batch_config(vr_batch batch, int32_t* wg_per_cu, int32_t* order, int32_t* staging,
                           int32_t* tile_width, int32_t* chunk_slices);
 

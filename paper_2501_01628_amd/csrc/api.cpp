@@ -723,8 +723,8 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
     return n;
 }
 
-// Whether the frame queue of storage group g (0 float32, 1 float16) marches
-// from HBM, with the context's current path: every path gives the same bits.
+// Whether a queue of jobs of one storage precision (g: 0 float32, 1 float16)
+// is faster marched from HBM than staged; every path gives the same bits.
 // Staging pays by the samples that a staged voxel serves and needs a
 // workgroup's LDS for each tile, so the direct march is the faster one
 // * when the tiles are few (2 per CU; 1.4 for float16 below half a voxel a
@@ -743,30 +743,56 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
 //   0.25, line at 0.57, 320^3: at 0.5 1.93 and 1.76, at 0.75 1.01 and 1.05;
 //   step 1, line at 1.13: at 1.0 339 us and 302, at 1.4 315 and 335).  float16
 //   bricks stage twice the voxels in the same LDS: direct is 0.64 to 1.04 times
-//   as fast there.
-// A staged configuration that the caller chose is taken as it is.
-static bool frame_direct(vr_context ctx, int g, const MarchParams* jobs, int n) {
-    if (ctx->path == kPathDirect) return true;
-    if (ctx->cfg_chosen[g]) return false;
-    // voxels a pixel at a brick's centre, over the line: weighted by its tiles
-    double tiles = 0.0, pixel = 0.0;
-    bool few = g == 0;                  // two tiles per CU are few
-    for (int i = 0; i < n; ++i) {
-        const CameraK& c = jobs[i].cam;
-        const BrickK& b = jobs[i].brick;
-        const double t = queue_tiles(jobs[i].roi_w, jobs[i].roi_h, 16);
+//   as fast there;
+// * for small bricks, whose voxels stay in the caches: float32 bricks that fit
+//   an XCD's 4 MB L2, or twice that up to 1.6 of the line above, and float16
+//   ones up to 8 MB from one voxel a pixel on, where few samples share a staged
+//   voxel (batches of 12 frames of 8 bricks at 512x512: of 24 to 64 voxels an
+//   edge 341 us staged and 239 direct, float16 243 and 227; of 48 to 160, 5 to 8
+//   MB a tile, 742 and 718, float16 639 and 494; the latter at 256x256, 4.6
+//   voxels a pixel, 441 and 451, at 1024x1024, 1.1 a pixel, 733 and 582; of 160
+//   to 256, 36 MB, at 384x384 2.03 ms and 2.75, float16 1.25 and 1.51; frames of
+//   320^3 in 27 bricks, 5 to 8 MB, at 1.0 voxels a pixel 1.06 to 1.25 times as
+//   fast, at 1.4 and 2.0 0.89 to 1.23).
+struct DirectRule {
+    int g, cus;
+    // sums weighted by a job's tiles: voxels a pixel at the brick's centre,
+    // the same over the line, bytes of the brick
+    double tiles = 0.0, pixel = 0.0, line = 0.0, bytes = 0.0;
+    bool few2;
+    DirectRule(int group, int cu_count) : g(group), cus(cu_count), few2(group == 0) {}
+    void add(const MarchParams& p) {
+        const CameraK& c = p.cam;
+        const BrickK& b = p.brick;
+        const double t = queue_tiles(p.roi_w, p.roi_h, 16);
         double depth = 1.0;
         if (c.kind == 0) {
             depth = 0.0;
             for (int k = 0; k < 3; ++k) depth += (0.5 * (b.lo[k] + b.hi[k]) - c.eye[k]) * c.f[k];
         }
         const double fine = std::min(b.spacing[0], std::min(b.spacing[1], b.spacing[2]));
-        tiles += t;
-        few = few || 2.0 * jobs[i].dt >= fine;
         const double vpp = std::fabs(depth) * 2.0 * c.ay / ((double)c.height * fine);
-        pixel += t * vpp / std::sqrt(1.28 * jobs[i].dt / fine);
+        few2 = few2 || 2.0 * p.dt >= fine;
+        tiles += t;
+        pixel += t * vpp;
+        line += t * vpp / std::sqrt(1.28 * p.dt / fine);
+        bytes += t * (g == 0 ? 4.0 : 2.0) * b.sdim[0] * b.sdim[1] * b.sdim[2];
     }
-    return tiles <= (few ? 2.0 : 1.4) * ctx->cus || (g == 0 && pixel <= tiles);
+    bool direct() const {
+        if (tiles <= (few2 ? 2.0 : 1.4) * cus) return true;
+        if (g == 1) return pixel >= tiles && bytes <= 8.0e6 * tiles;
+        return line <= tiles || bytes <= 4.0e6 * tiles || (bytes <= 8.0e6 * tiles && line <= 1.6 * tiles);
+    }
+};
+
+// ... for a frame with the context's path; a staged configuration that the
+// caller chose is taken as it is.
+static bool frame_direct(vr_context ctx, int g, const MarchParams* jobs, int n) {
+    if (ctx->path == kPathDirect) return true;
+    if (ctx->cfg_chosen[g]) return false;
+    DirectRule rule(g, ctx->cus);
+    for (int i = 0; i < n; ++i) rule.add(jobs[i]);
+    return rule.direct();
 }
 
 // Job table and tile prefix of a frame of n partials, grouped by storage
@@ -2341,6 +2367,8 @@ struct vr_batch_s {
     std::vector<BatchGroup> groups;
     int32_t wg_per_cu = 0, order = 0;
     int32_t staging = kStagingRing, tile_w = 32, chunk = 4;   // staged configuration of the tables
+    bool direct_pays[2] = {false, false};   // storage groups that DirectRule would march from HBM
+    bool direct = false;                    // the tables march those groups from HBM
     uint64_t shape_key = 0;
     hipStream_t cap = nullptr;
 };
@@ -2371,7 +2399,7 @@ void fnv(uint64_t& h, const void* p, size_t n) {
 // brick, with tickets of tile_w x 16 pixels; a tile prefix per queue and a
 // composite-block prefix per group.  Work already enqueued on the context
 // stream (an earlier launch of this batch reads the tables) finishes first.
-vr_status batch_upload_tables(vr_batch b, int order, int staging, int tile_w, int chunk) {
+vr_status batch_upload_tables(vr_batch b, int order, int staging, int tile_w, int chunk, bool direct) {
     const int n = (int)b->jobs.size();
     const int nf = (int)b->frames.size();
     const int G = b->n_groups;
@@ -2422,7 +2450,7 @@ vr_status batch_upload_tables(vr_batch b, int order, int staging, int tile_w, in
                 const int i = idx[k];
                 if (b->f16[i] != pass || job_group[i] != g) continue;
                 prefix.push_back(acc);
-                acc += queue_tiles(b->jobs[i].roi_w, b->jobs[i].roi_h, tile_w);
+                acc += queue_tiles(b->jobs[i].roi_w, b->jobs[i].roi_h, direct && b->direct_pays[pass] ? 16 : tile_w);
                 table.push_back(b->jobs[i]);
                 ++cnt;
             }
@@ -2463,6 +2491,7 @@ vr_status batch_upload_tables(vr_batch b, int order, int staging, int tile_w, in
     b->staging = staging;
     b->tile_w = tile_w;
     b->chunk = chunk;
+    b->direct = direct;
     for (MarchParams& jp : b->jobs) {      // (single-partial fields; the queue passes its own)
         jp.staging = staging;
         jp.tile_w = tile_w;
@@ -2471,9 +2500,9 @@ vr_status batch_upload_tables(vr_batch b, int order, int staging, int tile_w, in
     return VR_OK;
 }
 
-vr_status batch_upload(vr_batch b, int order, int staging, int tile_w, int chunk) {
+vr_status batch_upload(vr_batch b, int order, int staging, int tile_w, int chunk, bool direct) {
     try {
-        return batch_upload_tables(b, order, staging, tile_w, chunk);
+        return batch_upload_tables(b, order, staging, tile_w, chunk, direct);
     } catch (const std::bad_alloc&) {
         return fail(b->ctx, VR_ERR_OUT_OF_MEMORY, "batch upload: out of host memory");
     }
@@ -2489,7 +2518,8 @@ void batch_drop_graph(vr_batch b) {
 }
 
 // Capture each group's launches (queue counters are reset by a kernel, so a
-// graph holds kernel nodes only) with `wg_per_cu` persistent workgroups per CU.
+// graph holds kernel nodes only) with `wg_per_cu` persistent workgroups per CU
+// (direct groups: as many as fit).
 vr_status batch_capture(vr_batch b, int wg_per_cu) {
     vr_context ctx = b->ctx;
     batch_drop_graph(b);
@@ -2498,6 +2528,10 @@ vr_status batch_capture(vr_batch b, int wg_per_cu) {
     const CompositeParams* dframes = reinterpret_cast<const CompositeParams*>(b->ws + b->off_cframes);
     const int32_t* dcprefix = reinterpret_cast<const int32_t*>(b->ws + b->off_cprefix);
     int32_t* heads = reinterpret_cast<int32_t*>(b->ws);
+    auto staged = [&](int g) { return b->direct && b->direct_pays[g] ? 0 : 1; };
+    auto workgroups = [&](int g) {
+        return staged(g) ? wg_per_cu * ctx->cus : queue_workgroups(ctx, g == 1 ? kF16 : kF32, false, 0, 0, 0);
+    };
     for (auto& q : b->groups) {
         hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) {
@@ -2506,14 +2540,14 @@ vr_status batch_capture(vr_batch b, int wg_per_cu) {
         }
         hipError_t le = hipSuccess;
         if (q.n32 > 0) {
-            QueueParams qp{djobs + q.job0, dprefix + q.pre32, q.n32, q.total32, heads, 1,
+            QueueParams qp{djobs + q.job0, dprefix + q.pre32, q.n32, q.total32, heads, staged(0),
                            b->staging, b->tile_w, b->chunk, err_word(ctx)};
-            le = launch_march_queue(qp, kF32, wg_per_cu * ctx->cus, b->cap);
+            le = launch_march_queue(qp, kF32, workgroups(0), b->cap);
         }
         if (le == hipSuccess && q.n16 > 0) {
-            QueueParams qp{djobs + q.job0 + q.n32, dprefix + q.pre16, q.n16, q.total16, heads + kQueueParts, 1,
+            QueueParams qp{djobs + q.job0 + q.n32, dprefix + q.pre16, q.n16, q.total16, heads + kQueueParts, staged(1),
                            b->staging, b->tile_w, b->chunk, err_word(ctx)};
-            le = launch_march_queue(qp, kF16, wg_per_cu * ctx->cus, b->cap);
+            le = launch_march_queue(qp, kF16, workgroups(1), b->cap);
         }
         if (le == hipSuccess && q.f1 > q.f0)
             le = launch_composite_many(dframes + q.f0, dcprefix + q.cpre, q.f1 - q.f0, q.ctotal, b->cap);
@@ -2666,10 +2700,21 @@ static vr_status batch_create(vr_context ctx, int32_t n_cameras, const vr_camera
     if (e != hipSuccess) return fail(ctx, VR_ERR_DEVICE, "%s: %s", who, hipGetErrorString(e));
     e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
     if (e != hipSuccess) return fail(ctx, VR_ERR_DEVICE, "%s: %s", who, hipGetErrorString(e));
-    // until tuned, the context's configuration of the storage with more jobs
+    // until tuned, the direct march where the rule says so, and else the
+    // context's configuration of the storage with more jobs
+    for (int g2 = 0; g2 < 2; ++g2) {
+        DirectRule rule(g2, ctx->cus);
+        bool any = false;
+        for (size_t i = 0; i < b->jobs.size(); ++i)
+            if (b->f16[i] == g2) {
+                rule.add(b->jobs[i]);
+                any = true;
+            }
+        b->direct_pays[g2] = any && !ctx->cfg_chosen[g2] && rule.direct();
+    }
     const long long n16 = std::count(b->f16.begin(), b->f16.end(), 1);
     const MarchCfg& mc = ctx->cfg[n16 > (long long)b->f16.size() - n16 ? 1 : 0];
-    vr_status st = batch_upload(b.get(), 0, mc.staging, mc.tile_w, mc.chunk);
+    vr_status st = batch_upload(b.get(), 0, mc.staging, mc.tile_w, mc.chunk, true);
     if (st == VR_OK) st = batch_capture(b.get(), max_wg_per_cu(b.get(), mc.staging, mc.tile_w, mc.chunk));
     if (st != VR_OK) {
         batch_destroy(b.get());
@@ -2715,7 +2760,7 @@ vr_status vr_batch_set_groups(vr_batch b, int32_t n_groups) {
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, VR_ERR_DEVICE, "vr_batch_set_groups: cannot select device %d", ctx->device);
     b->n_groups = n_groups;
-    vr_status st = batch_upload(b, b->order, b->staging, b->tile_w, b->chunk);
+    vr_status st = batch_upload(b, b->order, b->staging, b->tile_w, b->chunk, b->direct);
     if (st == VR_OK) st = batch_capture(b, b->wg_per_cu);
     return st == VR_OK ? ok(ctx) : st;
 }
@@ -2771,6 +2816,7 @@ namespace {
 
 struct TuneChoice {
     int wg, order, staging, tile_w, chunk;
+    bool direct;
 };
 
 // Staged configurations the autotuner times: slab, and ring with 16- or
@@ -2779,7 +2825,8 @@ constexpr int kTuneConfigs[5][3] = {
     {kStagingSlab, 16, 4}, {kStagingRing, 16, 4}, {kStagingRing, 16, 8}, {kStagingRing, 32, 4}, {kStagingRing, 32, 8}};
 
 // Autotuner cache: one line per tuned batch shape,
-// "key wg order staging tile chunk ms".
+// "key wg order staging tile chunk ms" (staging + 2: with the direct march of
+// the groups that the rule names).
 bool cache_lookup(const char* path, uint64_t key, TuneChoice* c) {
     if (!path) return false;
     FILE* f = std::fopen(path, "r");
@@ -2793,6 +2840,8 @@ bool cache_lookup(const char* path, uint64_t key, TuneChoice* c) {
         if (std::sscanf(line, "%llx %d %d %d %d %d %lf", &k, &t.wg, &t.order, &t.staging, &t.tile_w, &t.chunk,
                         &ms) == 7 &&
             k == key) {
+            t.direct = t.staging >= 2;
+            if (t.direct) t.staging -= 2;
             *c = t;
             found = true;
         }
@@ -2805,18 +2854,19 @@ void cache_store(const char* path, uint64_t key, const TuneChoice& c, double ms)
     if (!path) return;
     FILE* f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "%llx %d %d %d %d %d %.6f\n", (unsigned long long)key, c.wg, c.order, c.staging, c.tile_w,
-                 c.chunk, ms);
+    std::fprintf(f, "%llx %d %d %d %d %d %.6f\n", (unsigned long long)key, c.wg, c.order,
+                 c.staging + (c.direct ? 2 : 0), c.tile_w, c.chunk, ms);
     std::fclose(f);
 }
 
 bool choice_valid(const vr_batch b, const TuneChoice& c) {
     return valid_march_config(c.staging, c.tile_w, c.chunk) && (c.order == 0 || c.order == 1) && c.wg >= 1 &&
-           c.wg <= max_wg_per_cu(b, c.staging, c.tile_w, c.chunk);
+           c.wg <= max_wg_per_cu(b, c.staging, c.tile_w, c.chunk) &&
+           (!c.direct || b->direct_pays[0] || b->direct_pays[1]);
 }
 
 vr_status apply_choice(vr_batch b, const TuneChoice& c) {
-    vr_status st = batch_upload(b, c.order, c.staging, c.tile_w, c.chunk);
+    vr_status st = batch_upload(b, c.order, c.staging, c.tile_w, c.chunk, c.direct);
     if (st == VR_OK) st = batch_capture(b, c.wg);
     return st;
 }
@@ -2840,33 +2890,41 @@ vr_status vr_batch_autotune(vr_batch b, int32_t reps, double* best_ms) {
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return fail(ctx, VR_ERR_DEVICE, "vr_batch_autotune: cannot create events");
     double best = 1e300;
-    TuneChoice bc{b->wg_per_cu, b->order, b->staging, b->tile_w, b->chunk};
+    TuneChoice bc{b->wg_per_cu, b->order, b->staging, b->tile_w, b->chunk, b->direct};
     vr_status st = VR_OK;
-    // candidates: staged configuration x job order x persistent workgroups per CU
+    auto time_choice = [&](const TuneChoice& c) {       // the tables are uploaded for it
+        st = batch_capture(b, c.wg);
+        if (st != VR_OK) return;
+        hipError_t e = batch_replay(b, ctx->stream, false);   // warm-up
+        if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
+        for (int r = 0; r < reps && e == hipSuccess; ++r) e = batch_replay(b, ctx->stream, false);
+        if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        if (e != hipSuccess) {
+            st = fail(ctx, VR_ERR_DEVICE, "vr_batch_autotune: %s", hipGetErrorString(e));
+            return;
+        }
+        const double per = ms / reps;
+        if (per < best) {
+            best = per;
+            bc = c;
+        }
+    };
+    // candidates: staged configuration x job order x persistent workgroups per
+    // CU, and the direct march of the groups it pays for x job order
+    const int ds = b->staging, dw = b->tile_w, dc = b->chunk;
+    for (int order = 0; order < 2 && st == VR_OK && (b->direct_pays[0] || b->direct_pays[1]); ++order) {
+        st = batch_upload(b, order, ds, dw, dc, true);
+        if (st == VR_OK) time_choice(TuneChoice{max_wg_per_cu(b, ds, dw, dc), order, ds, dw, dc, true});
+    }
     for (const auto& cfg : kTuneConfigs) {
         for (int order = 0; order < 2 && st == VR_OK; ++order) {
-            st = batch_upload(b, order, cfg[0], cfg[1], cfg[2]);
+            st = batch_upload(b, order, cfg[0], cfg[1], cfg[2], false);
             const int maxwg = max_wg_per_cu(b, cfg[0], cfg[1], cfg[2]);
-            for (int wg = 1; wg <= maxwg && st == VR_OK; ++wg) {
-                st = batch_capture(b, wg);
-                if (st != VR_OK) break;
-                hipError_t e = batch_replay(b, ctx->stream, false);   // warm-up
-                if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
-                for (int r = 0; r < reps && e == hipSuccess; ++r) e = batch_replay(b, ctx->stream, false);
-                if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
-                if (e == hipSuccess) e = hipEventSynchronize(e1);
-                float ms = 0.f;
-                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-                if (e != hipSuccess) {
-                    st = fail(ctx, VR_ERR_DEVICE, "vr_batch_autotune: %s", hipGetErrorString(e));
-                    break;
-                }
-                const double per = ms / reps;
-                if (per < best) {
-                    best = per;
-                    bc = TuneChoice{wg, order, cfg[0], cfg[1], cfg[2]};
-                }
-            }
+            for (int wg = 1; wg <= maxwg && st == VR_OK; ++wg)
+                time_choice(TuneChoice{wg, order, cfg[0], cfg[1], cfg[2], false});
         }
     }
     (void)hipEventDestroy(e0);
