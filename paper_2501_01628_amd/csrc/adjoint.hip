@@ -12,18 +12,18 @@
 //   R_k = a_k rgb_k + (1 - a_k) R_{k+1},  Q_k = (1 - a_k) Q_{k+1}
 // (R = colour, Q = transmittance of what lies behind sample k in the brick),
 //   dC/drgb_k = T_k a_k,  dC/da_k = T_k (rgb_k - R_{k+1}),  dA/da_k = T_k Q_{k+1}.
-// The transmittance T_k in front of a sample is that in front of the stretch
-// times that of the stretch up to a sample behind, times exp2 of the a'
-// between; the sum is kept as an integer and a fraction, so that T_k is as
-// exact as one exponential.
+// The transmittance T_k in front of a sample is exp2 of the a' summed up to it:
+// forward over the ray's stretches, taken off again on the way back, the sum as
+// an integer and a fraction, so that T_k is nearly as exact as one exponential
+// (a product over the ray gathers two roundings a sample).
 // One lane per ray, from transmittance checkpoints, left the GPU to its
 // longest rays: at 512x512 on 128^3 the slowest of 3,016 wavefronts ran 3.4
 // times the average, 2 to 3 per SIMD.  Bound by the vector ALU (60 % of its
 // issue slots, 70 % of the lanes active) and by the voxel atomics (13 % of the
 // time of 128^3 at 512x512, 36 % of 16 bricks of 512 x 256 x 256 at 384x384).
 // Forward and backward of 8 views of the former, step 0.5: 8.03 ms before,
-// 4.79 now; of one view of the latter, float16, step 0.25: 5.33 ms before, 3.69
-// now.  8 lanes a ray: 4.84 and 4.16 ms (set-up and partly filled stretches).
+// 4.85 now; of one view of the latter, float16, step 0.25: 5.33 ms before, 3.91
+// now.  8 lanes a ray: 1 % and 12 % slower (set-up, partly filled stretches).
 // The opacity a_k = 1 - exp2(-a'_k) with a' the pre-scaled table opacity;
 // table gradients are summed per lane while consecutive samples use one
 // table segment, accumulated per workgroup in LDS (ds_add_f32) and flushed
@@ -41,6 +41,14 @@ namespace {
 constexpr int kTile = 8;
 constexpr int kParts = 4;               // lanes per ray
 constexpr int kThreads = 64 * kParts;   // an 8x8 tile
+// A workgroup takes kSeries tiles one after the other where that leaves kFill
+// workgroups (4 on each of 256 CUs; many partials: always): the table gradient
+// is added to global memory once a workgroup, and every such float add rounds
+// at the size of the whole sum.  One tile a workgroup is 2 % (one brick) to 5 %
+// (16 bricks) faster, but the gradients' error against float64 grew from 2.8e-7
+// to 4.6e-7 on a scene of several bricks, where this leaves it as it was.
+constexpr int kSeries = 4;
+constexpr int kFill = 1024;
 constexpr float kLn2 = 0.6931471805599453f;
 
 // Where a ray's samples lie: position, corner reads and stored cell of sample
@@ -220,13 +228,20 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
             tacc[i] = 0.f;
         }
     };
-    // forward: colour and transmittance of the stretch; kt, Ft: the last
-    // sample (from the stretch's first) in front of which its transmittance is
-    // a normal float, and that
-    constexpr float kNormal = 0x1p-126f;
-    float C0 = 0.f, C1 = 0.f, C2 = 0.f, F = 1.f, Ft = 1.f;
-    int kt = 0;
-    auto ahead = [&](const auto& a, int k) {
+    // a' summed over samples, as sn + sf (a' above 1024, which leaves no
+    // transmittance, counts as 1024: sn stays small)
+    int sn = 0;
+    float sf = 0.0f;
+    auto sum_a = [&](float a) {
+        sf += a;
+        const float whole = rintf(sf);
+        sf -= whole;
+        sn += (int)whole;
+    };
+    constexpr float kMostA = 1024.0f;
+    // forward: colour and transmittance of the stretch, and its sum of a'
+    float C0 = 0.f, C1 = 0.f, C2 = 0.f, F = 1.f;
+    auto ahead = [&](const auto& a) {
         const Classified e = classify(tft, reads.value(a), tf_k, tf_o);
         const float Fn = F * trans_exp2(-e.a);
         const float w = F - Fn;
@@ -234,30 +249,32 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
         C1 = fmaf(w, e.g, C1);
         C2 = fmaf(w, e.b, C2);
         F = Fn;
-        if (F >= kNormal) {
-            kt = k + 1;
-            Ft = F;
-        }
+        sum_a(fminf(e.a, kMostA));
     };
     blocks_forward(k0, k1, [&](long long kA, int lo, int hi) {
         const Anchor an = make_anchor(rs, b, p.dt, kA);
-        const int m = (int)(kA - k0);
         reads.anchor(an);
         for (int j = lo; j <= hi; j += 2) {
             const auto a0 = reads.read(an, st, (float)j);
             const auto a1 = reads.read(an, st, (float)(j + 1));
             __builtin_amdgcn_sched_barrier(0);
-            ahead(a0, m + j);
-            if (j < hi) ahead(a1, m + j + 1);
+            ahead(a0);
+            if (j < hi) ahead(a1);
         }
     });
-    // the ray's stretches: transmittance in front of this one, and R, Q behind it
-    float front = 1.f, R0 = 0.f, R1 = 0.f, R2 = 0.f, Q = 1.f;
+    // the ray's stretches: a' in front of this one, and R, Q behind it
+    const int own_n = sn;
+    const float own_f = sf;
+    float R0 = 0.f, R1 = 0.f, R2 = 0.f, Q = 1.f;
     const int first = (threadIdx.x & 63) - part * (64 / kParts);
 #pragma unroll
     for (int q = 0; q < kParts; ++q) {
-        const float Fq = __shfl(F, first + q * (64 / kParts));
-        if (q < part) front *= Fq;
+        const int nq = __shfl(own_n, first + q * (64 / kParts));
+        const float fq = __shfl(own_f, first + q * (64 / kParts));
+        if (q < part) {
+            sn += nq;
+            sum_a(fq);
+        }
     }
 #pragma unroll
     for (int q = kParts - 1; q > 0; --q) {
@@ -271,19 +288,12 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
         }
     }
     {
-        float sf = 0.0f;                // T_k = front Ft 2^(sn + sf) for k <= kt; samples behind kt see none
-        int sn = 0;
-        auto back = [&](const auto& a, const Anchor& an, float fj, int k) {
+        auto back = [&](const auto& a, const Anchor& an, float fj) {
             const Classified e = classify(tft, reads.value(a), tf_k, tf_o);
             const float om = trans_exp2(-e.a);          // 1 - alpha
             const float al = 1.0f - om;
-            if (k < kt) {
-                sf += e.a;
-                const float whole = rintf(sf);
-                sf -= whole;
-                sn += (int)whole;
-            }
-            const float Tk = k > kt ? 0.0f : front * ldexpf(Ft * trans_exp2(sf), sn);
+            sum_a(-fminf(e.a, kMostA));
+            const float Tk = ldexpf(trans_exp2(-sf), -sn);
             const float ta = Tk * al;
             const float d_r = g.x * ta, d_g = g.y * ta, d_b = g.z * ta;
             const float d_al = Tk * (g.x * (e.r - R0) + g.y * (e.g - R1) + g.z * (e.b - R2) + g.w * Q);
@@ -330,15 +340,14 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
         };
         blocks_back(k0, k1, [&](long long kA, int lo, int hi) {
             const Anchor an = make_anchor(rs, b, p.dt, kA);
-            const int m = (int)(kA - k0);
             reads.anchor(an);
             for (int j = hi; j >= lo; j -= 2) {
                 const float f0 = (float)j, f1 = (float)(j - 1);
                 const auto a0 = reads.read(an, st, f0);
                 const auto a1 = reads.read(an, st, f1);
                 __builtin_amdgcn_sched_barrier(0);
-                back(a0, an, f0, m + j);
-                if (j > lo) back(a1, an, f1, m + j - 1);
+                back(a0, an, f0);
+                if (j > lo) back(a1, an, f1);
             }
         });
     }
@@ -346,9 +355,9 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
     tflush();
 }
 
-// One workgroup's work: tile `tile` of the partial (p, bp).
+// One workgroup's work: tiles block, block + blocks, ... of the partial (p, bp).
 template <typename TS>
-__device__ __forceinline__ void backward_tile(const MarchParams& p, const BackwardParams& bp, int tile) {
+__device__ __forceinline__ void backward_tiles(const MarchParams& p, const BackwardParams& bp, int block, int blocks) {
     __shared__ TFTable tft;
     __shared__ float gtf[256 * 4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -359,21 +368,23 @@ __device__ __forceinline__ void backward_tile(const MarchParams& p, const Backwa
     // a wavefront's 64 / kParts pixels: a 4 x 4 quarter of the tile
     static_assert(kParts == 4, "a wavefront takes a 4 x 4 quarter of the tile");
     const int q = lane & 15, part = lane >> 4;
-    const int lx = tile % p.tiles_x * kTile + (wave & 1) * 4 + (q & 3);
-    const int ly = tile / p.tiles_x * kTile + (wave >> 1) * 4 + (q >> 2);
     const float tf_k = 255.0f / (p.tf.vmax - p.tf.vmin);
     const float tf_o = -p.tf.vmin * tf_k;
-    RaySetup rs;
-    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-    bool has = lx < p.roi_w && ly < p.roi_h && setup_ray(p.cam, p.brick, p.dt, p.roi_x0 + lx, p.roi_y0 + ly, rs);
-    if (has) {
-        g = reinterpret_cast<const float4*>(bp.d_part)[(long long)ly * p.roi_w + lx];
-        has = g.x != 0.f || g.y != 0.f || g.z != 0.f || g.w != 0.f;
+    for (int tile = block; tile < p.tiles_x * p.tiles_y; tile += blocks) {
+        const int lx = tile % p.tiles_x * kTile + (wave & 1) * 4 + (q & 3);
+        const int ly = tile / p.tiles_x * kTile + (wave >> 1) * 4 + (q >> 2);
+        RaySetup rs;
+        float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+        bool has = lx < p.roi_w && ly < p.roi_h && setup_ray(p.cam, p.brick, p.dt, p.roi_x0 + lx, p.roi_y0 + ly, rs);
+        if (has) {
+            g = reinterpret_cast<const float4*>(bp.d_part)[(long long)ly * p.roi_w + lx];
+            has = g.x != 0.f || g.y != 0.f || g.z != 0.f || g.w != 0.f;
+        }
+        if (fits_rows(p.brick, sizeof(TS)))
+            backward_ray(p, bp, tft, gtf, rs, has, part, g, tf_k, tf_o, RowReads<TS>(p.brick));
+        else
+            backward_ray(p, bp, tft, gtf, rs, has, part, g, tf_k, tf_o, AnyReads<TS>(p.brick));
     }
-    if (fits_rows(p.brick, sizeof(TS)))
-        backward_ray(p, bp, tft, gtf, rs, has, part, g, tf_k, tf_o, RowReads<TS>(p.brick));
-    else
-        backward_ray(p, bp, tft, gtf, rs, has, part, g, tf_k, tf_o, AnyReads<TS>(p.brick));
     __syncthreads();
     for (int e = threadIdx.x; e < 1024; e += kThreads) {
         const float v = gtf[e];
@@ -382,15 +393,15 @@ __device__ __forceinline__ void backward_tile(const MarchParams& p, const Backwa
 }
 
 template <typename TS>
-__global__ __launch_bounds__(kThreads) void march_backward(MarchParams p, BackwardParams bp) {
-    backward_tile<TS>(p, bp, blockIdx.x);
+__global__ __launch_bounds__(kThreads, 4) void march_backward(MarchParams p, BackwardParams bp) {
+    backward_tiles<TS>(p, bp, blockIdx.x, gridDim.x);
 }
 
-// Many partials in one launch: workgroup b takes a tile of job j, the last j
+// Many partials in one launch: workgroup b takes tiles of job j, the last j
 // with block_start[j] <= b (so that partials of few tiles still fill the GPU
 // together).
 template <typename TS>
-__global__ __launch_bounds__(kThreads) void march_backward_many(const BackwardJob* __restrict__ jobs,
+__global__ __launch_bounds__(kThreads, 4) void march_backward_many(const BackwardJob* __restrict__ jobs,
                                                                 const int32_t* __restrict__ block_start,
                                                                 int32_t n_jobs) {
     const int b = blockIdx.x;
@@ -401,12 +412,13 @@ __global__ __launch_bounds__(kThreads) void march_backward_many(const BackwardJo
     }
     lo = uniform_i(lo);      // uniform: the job's fields load as scalars
     const BackwardJob& J = const_entry(jobs, lo);
-    backward_tile<TS>(J.p, J.bp, b - uniform_i(block_start[lo]));
+    const int first = uniform_i(block_start[lo]);
+    backward_tiles<TS>(J.p, J.bp, b - first, uniform_i(block_start[lo + 1]) - first);
 }
 
 }  // namespace
 
-int backward_many_waves() { return 1; }
+int backward_many_waves() { return kSeries; }
 
 hipError_t launch_march_backward_many(const BackwardJob* jobs, const int32_t* block_start, int32_t n_jobs,
                                       int32_t total_blocks, StorageK storage, hipStream_t stream) {
@@ -424,10 +436,11 @@ hipError_t launch_march_backward(const MarchParams& p, const BackwardParams& bp,
                                  hipStream_t stream) {
     const int tiles = p.tiles_x * p.tiles_y;
     if (tiles == 0) return hipSuccess;
+    const int blocks = max((tiles + kSeries - 1) / kSeries, min(tiles, kFill));
     if (storage == kF16)
-        hipLaunchKernelGGL(march_backward<__half>, dim3(tiles), dim3(kThreads), 0, stream, p, bp);
+        hipLaunchKernelGGL(march_backward<__half>, dim3(blocks), dim3(kThreads), 0, stream, p, bp);
     else
-        hipLaunchKernelGGL(march_backward<float>, dim3(tiles), dim3(kThreads), 0, stream, p, bp);
+        hipLaunchKernelGGL(march_backward<float>, dim3(blocks), dim3(kThreads), 0, stream, p, bp);
     return hipGetLastError();
 }
 
