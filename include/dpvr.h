@@ -624,8 +624,8 @@ vr_status vr_rqc_plan(vr_context ctx, int32_t n, const vr_brick* bricks, void* w
 
 /* Render the frame of the last vr_rqc_plan (same workspace, bricks, camera
  * and dt, or VR_ERR_STATE) with the current transfer function and data:
- * n cycle steps of the shadow-ray queues (skipped when ambient = 1), n cycle
- * steps of the primary-ray queues, then per pixel the bricks' segments in
+ * the shadow rays through all bricks (skipped when ambient = 1), the primary
+ * rays through all bricks, then per pixel the bricks' segments in
  * depth order over bg.  shade: device, total_samples floats (ignored when
  * ambient = 1); out: device, height x width x 4 floats, 16-byte aligned;
  * samples: optional device counter (8-byte aligned) to which the primary and
@@ -786,7 +786,7 @@ vr_status vr_resolve_tetparts(vr_context ctx, int32_t n, const vr_tetpart* parts
  * index and a transmittance per slot).
  * vr_render_tetparts_shadowed: the frame of the last plan (same plan buffer,
  * parts, camera and dt, else VR_ERR_STATE): records the slots' sample
- * indices, runs n shadow cycle steps, marches the shaded runs and resolves
+ * indices, traces the shadow rays through all parts, marches the shaded runs and resolves
  * them into out over bg.  plan, slots: device, 256-byte aligned, kept by the
  * caller; samples (optional) counts primary and shadow samples held.
  * Errors: as vr_render_tetparts, VR_ERR_WORKSPACE for a short plan or slot

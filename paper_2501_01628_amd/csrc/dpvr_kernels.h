@@ -74,7 +74,8 @@ struct QueueParams {
     const int32_t* tile_start; // device, n_jobs + 1 entries (exclusive prefix of tiles)
     int32_t n_jobs;
     int32_t total_tiles;
-    int32_t* head;             // device, kQueueParts ticket counters (reset by the launcher)
+    int32_t* head;             // device, kQueueParts ticket counters (reset by the launcher; it passes NULL to the
+                               // kernels when every ticket has its workgroup)
     int32_t staged;            // 1: LDS-staged tiles, 0: every lane marches from HBM
     int32_t staging;           // kStagingSlab or kStagingRing
     int32_t tile_w;            // staged tile width (16, or 32 for the ring)
