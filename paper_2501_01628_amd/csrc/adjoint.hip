@@ -229,14 +229,18 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
         }
     };
     // a' summed over samples, as sn + sf (a' above 1024, which leaves no
-    // transmittance, counts as 1024: sn stays small)
+    // transmittance, counts as 1024: sn stays small).  The integer part is
+    // split off before the addition: adding a whole dense a' to the fraction
+    // would round it at the size of that a', and the walk back would leave the
+    // rounding in front of the dense sample, where T_k is still near 1.
     int sn = 0;
     float sf = 0.0f;
     auto sum_a = [&](float a) {
-        sf += a;
-        const float whole = rintf(sf);
-        sf -= whole;
-        sn += (int)whole;
+        const float most = rintf(a);
+        sf += a - most;                  // |a - most| <= 1/2, exact
+        const float carry = rintf(sf);
+        sf -= carry;
+        sn += (int)(most + carry);
     };
     constexpr float kMostA = 1024.0f;
     // forward: colour and transmittance of the stretch, and its sum of a'
