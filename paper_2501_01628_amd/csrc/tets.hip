@@ -231,12 +231,13 @@ __global__ __launch_bounds__(256) void tet_affine(TetPartK P, double2_t* __restr
     out[(long long)P.n_tets + e] = double2_t{g[2], c};
 }
 
-// The samples k0 .. k1 (none if k1 < k0; both in [0, 2^31)) of ray r in part
-// P, in order: held(k, value) for a sample that a tetrahedron holds, gap()
-// for a stretch of samples that none holds.  A sample is sought by a walk from
-// the previous sample's tetrahedron (kWalkSteps tests, each step across the
-// face that rejects it most), then among the tetrahedra listed in its grid
-// cell (or in the BVH).
+// The samples k0 .. k1 (none if k1 < k0; k0 >= 0, fewer than 2^31 of them) of
+// ray r in part P, in order: held(k, value) for a sample that a tetrahedron
+// holds, gap() for a stretch of samples that none holds; k is a double (exact;
+// a shadow ray may meet a part after more than 2^31 samples).  A sample is
+// sought by a walk from the previous sample's tetrahedron (kWalkSteps tests,
+// each step across the face that rejects it most), then among the tetrahedra
+// listed in its grid cell (or in the BVH).
 //
 // Vector-memory instructions bound this (a 16-byte load of 64 scattered lanes
 // takes the L1 33 to 65 cycles, 17 where four neighbouring lanes share a
@@ -254,7 +255,7 @@ template <int kLocator, bool kValues, typename Held, typename Gap>
 __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, double dt, long long k0, long long k1,
                                           Held held, Gap gap) {
 #pragma clang fp contract(off)
-    unsigned k = (unsigned)k0;
+    double k = (double)k0;
     int left = k1 >= k0 ? (int)(k1 - k0) : -1;           // samples after this one
     int cand = -1;                                       // tetrahedron to test (-1: look the sample's cell up)
     int walk = 0;                                        // walk steps left (0: cand is from the cell's list)
@@ -266,7 +267,7 @@ __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, do
     const float per_cell = (float)fmin(0.999 / move, 1e6);       // samples per cell moved
     double x[3];                                         // the sample relative to the grid origin
     auto point = [&](double p[3]) {
-        const double t = ((double)k + 0.5) * dt;
+        const double t = (k + 0.5) * dt;
         for (int c = 0; c < 3; ++c) p[c] = r.o[c] + t * r.d[c];
     };
     auto place = [&]() {
@@ -335,14 +336,14 @@ __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, do
                     point(p);
                     v = tet_value(P, found, x, p);
                 }
-                held((int)k, v);
+                held(k, v);
             } else {
                 gap();
             }
             cand = found;
             walk = kWalkSteps;
             q = qend;
-            k += (unsigned)settle;
+            k += (double)settle;
             left = settle > left ? -1 : left - settle;
             place();
         }
@@ -434,12 +435,12 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
     }
     if constexpr (!kRuns) {
         unsigned long long held = 0;
-        walk_part<kLocator, false>(P, r, f.dt, k0, k1, [&](int k, float) {
+        walk_part<kLocator, false>(P, r, f.dt, k0, k1, [&](double k, float) {
             // the passes locate alike, so a ray holds as many samples as
             // counted; a mismatch (which only a logic error could cause) is
             // reported and never writes outside the ray's slots
             if (kMode == kTetRecord) {
-                if ((long long)held < slots) f.slot_k[slot0 + (long long)held] = k;
+                if ((long long)held < slots) f.slot_k[slot0 + (long long)held] = (int)k;
                 else if (f.err) atomicOr(f.err, kErrRange);
             }
             ++held;
@@ -503,8 +504,9 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
             ++nrun;
             in_run = false;
         };
-        walk_part<kLocator, true>(P, r, f.dt, ka, kb, [&](int k, float v) {
+        walk_part<kLocator, true>(P, r, f.dt, ka, kb, [&](double sample, float v) {
 #pragma clang fp contract(off)
+            const int k = (int)sample;
             if (!in_run) {
                 in_run = true;
                 key = k;
@@ -632,11 +634,11 @@ __global__ __launch_bounds__(256, 5) void tet_shadow(TetFrameParams f) {
             const TetPartK& at = const_entry(f.parts, h);
             float S = 1.0f;
             long long j0 = 0, j1 = -1;
-            if (at.n_tets > 0 && box_range(sr, at.lo, at.hi, f.dt, j0, j1) && j1 > 0x7fffffffLL) {
+            if (at.n_tets > 0 && box_range(sr, at.lo, at.hi, f.dt, j0, j1) && j1 - j0 > 0x7ffffffeLL) {
                 if (f.err) atomicOr(f.err, kErrRange);
                 j1 = j0 - 1;
             }
-            walk_part<kLocator, true>(at, sr, f.dt, j0, j1, [&](int, float v) {
+            walk_part<kLocator, true>(at, sr, f.dt, j0, j1, [&](double, float v) {
                 S = S * trans_exp2(-classify(tft, v, tf_k, tf_o).a);
                 ++evaluated;
             }, []() {});
