@@ -3,6 +3,7 @@
 // camera frame, region-of-interest projection and kernel launches.
 #include <hip/hip_runtime_api.h>
 
+#include <cfloat>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -1765,7 +1766,9 @@ vr_status vr_render_rqc(vr_context ctx, int32_t n, const vr_brick* bricks, const
     p.inv_dt = 1.0 / ctx->dt;
     for (int c = 0; c < 3; ++c) {
         p.light[c] = light->direction[c] / ln;
-        p.inv_light[c] = 1.0 / p.light[c];
+        // (the largest double for a component below its reciprocal: with an
+        // infinite one a sample on a brick's face would be 0 * infinity from it)
+        p.inv_light[c] = std::copysign(std::min(1.0 / std::fabs(p.light[c]), DBL_MAX), p.light[c]);
     }
     p.ert_eps = ctx->ert_eps;
     p.ambient = light->ambient;

@@ -1,5 +1,6 @@
 """Shadow rays at the ends of their range: a mesh part that they reach after
-more than 2^31 samples."""
+more than 2^31 samples, and a light whose direction has a component too small
+to have a reciprocal."""
 import numpy as np
 import pytest
 
@@ -44,3 +45,30 @@ def test_part_beyond_two_to_the_31_shadow_samples():
     assert total_far == total > 0 and held > total
     assert abs(held_far - held) <= 1e-3 * held            # points on faces may round to either side
     assert np.max(np.abs(far - near)) <= 1e-5
+
+
+def test_light_component_without_a_reciprocal():
+    """A direction component of 1e-310 moves no sample, so the image is that
+    of a zero component: also for samples exactly on a brick's lower face,
+    whose distance to it is zero."""
+    import paper_2501_01628_amd as dp
+    dims = (8, 8, 8)
+    rng = np.random.default_rng(7)
+    field = rng.uniform(0.0, 1.0, dims).astype(np.float32)
+    boxes = [((0, 0, 0), (8, 4, 8)), ((0, 4, 0), (8, 8, 8))]
+    # the middle row of pixels sees exactly y = 4
+    cam = dict(kind="orthographic", eye=(4.0, 4.0, -16.0), dir=(0.0, 0.0, 1.0), up=(0.0, 1.0, 0.0), view_height=9.0,
+               width=9, height=9)
+    sc = synth.scene_from_field("light", field, boxes, synth.default_tf(), cam, 0.5, 1.5)
+    imgs = []
+    for light in ((1.0, 0.0, 0.0), (1.0, 1e-310, 0.0)):
+        r = dp.Renderer([(b.voxels, b.lo) for b in sc.bricks], sc.tf, sc.vrange, sc.opacity_scale, sc.step, 0.0)
+        try:
+            r.set_camera(cam)
+            r.rqc_plan()
+            out = r.render_rqc(light, 0.1, BG)
+            r.synchronize()
+            imgs.append(out.cpu().numpy().copy())
+        finally:
+            r.close()
+    assert np.max(np.abs(imgs[1] - imgs[0])) <= 1e-6
