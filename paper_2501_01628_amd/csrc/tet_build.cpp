@@ -198,6 +198,13 @@ static void build_cell_heads(TetTables& out) {
 // 6 u |m_i|_1 X per coordinate, so 9 u M X for their sum and 6 u M X + 3 u for
 // the subtractions from one (M X >= 1); the float64 evaluation on both sides
 // 2^-49 M (X + |glo|).  16 u M X with the doubled extent bounds it twice over.
+// A step longer than the part takes samples further out than X; there the
+// bound need not hold, but the test still cannot accept: it accepts coordinates
+// above the bound only, which sum to one, so the bound (32 u M times the extent
+// L) is below 1/4 and u M L below 1/128, each coordinate lies in (0, 1), and a
+// point at distance R per axis, being the true coordinates' combination of the
+// vertices, has R <= L + 15 u M R L, so R <= 1.14 L.  (Rejecting such a point
+// is right.)
 static void build_planes32(TetTables& out) {
     double X = 0.0, G = 0.0;
     for (int c = 0; c < 3; ++c) {
