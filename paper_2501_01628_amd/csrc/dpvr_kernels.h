@@ -199,6 +199,11 @@ hipError_t launch_composite_backward(const CompositeParams& p, const CompositeBa
                                      hipStream_t stream);
 hipError_t launch_gather(const GatherParams& g, void* dst, StorageK storage, hipStream_t stream);
 
+// Tiles of one launch that takes a workgroup of up to 256 threads for each
+// (a grid axis holds fewer than 2^32 threads, and the ROIs of one 32768 x 32768
+// view already have 2^24 tiles of 8 x 8 pixels).
+constexpr int32_t kMaxLaunchTiles = 1 << 22;
+
 // Ray-queue cycling (rqc.hip): bricks as ranks, one directional light.
 struct RqcBrick {
     BrickK brick;
@@ -219,6 +224,7 @@ struct RqcParams {
     int32_t shadows;            // 0: a0 = 1, no shadow rays traced
     int32_t n;                  // bricks (ranks)
     int32_t tiles;              // 8 x 8 pixel tiles of all bricks' ROIs
+    int32_t tile0;              // first tile of a launch of the shadow rays
     int32_t width, height;
     const RqcBrick* bricks;     // device, n
     long long n_entries;        // sum of ROI pixels over the bricks

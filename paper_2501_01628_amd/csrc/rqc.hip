@@ -278,7 +278,7 @@ __global__ __launch_bounds__(256) void rqc_shadow(RqcParams p) {
     }
     __syncthreads();
     // the tile's brick: the last whose tiles begin at or before it
-    int tile = blockIdx.x, h = 0;
+    int tile = p.tile0 + (int)blockIdx.x, h = 0;
     for (; h + 1 < p.n; ++h) {
         const RqcBrick& rb = const_entry(p.bricks, h);
         const int t = (rb.roi_w + 7) / 8 * ((rb.roi_h + 7) / 8);
@@ -456,7 +456,9 @@ hipError_t launch_rqc_frame(RqcParams p, int cus, hipStream_t stream) {
     (void)cus;
     const long long npx = (long long)p.width * p.height;
     if (p.shadows && p.total > 0)
-        hipLaunchKernelGGL(rqc_shadow, dim3(p.tiles, kShadowSplit / 4), dim3(256), 0, stream, p);
+        for (p.tile0 = 0; p.tile0 < p.tiles; p.tile0 += kMaxLaunchTiles)
+            hipLaunchKernelGGL(rqc_shadow, dim3(min(p.tiles - p.tile0, kMaxLaunchTiles), kShadowSplit / 4), dim3(256),
+                               0, stream, p);
     const int tiles = (p.width + 7) / 8 * ((p.height + 7) / 8);
     hipLaunchKernelGGL(rqc_primary, dim3((tiles + 3) / 4, p.n), dim3(256), 0, stream, p);
     hipLaunchKernelGGL(rqc_resolve, dim3(grid_for(npx, 256)), dim3(256), 0, stream, p);
