@@ -45,6 +45,7 @@ struct TetFrameParams {
     const TetPartK* parts;      // device, n
     const int32_t* tile_start;  // device, n + 1: exclusive prefix of tiles (tet_tiles)
     int32_t n, total_tiles, max_runs;
+    int32_t tile0;              // first tile of a launch
     int32_t width, height;
     float bg[4];
     float* out;                 // height x width x 4

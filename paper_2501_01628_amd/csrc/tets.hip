@@ -412,7 +412,7 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
         __syncthreads();
     }
     int lx, ly;
-    const int j = tile_pixel(f, blockIdx.x, lx, ly);
+    const int j = tile_pixel(f, f.tile0 + (int)blockIdx.x, lx, ly);
     const TetPartK& P = const_entry(f.parts, j);
     const bool live = lx < P.roi_w && ly < P.roi_h;
     const long long npix = (long long)P.roi_w * P.roi_h;
@@ -587,8 +587,7 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
     count_held(f.samples, counted);
 }
 
-// The shadow rays of one tile of a home part's ROI (blockIdx.x, the tiles of
-// the march): the ray of every held primary sample (its slot) cycles through
+// The shadow rays of one tile of a home part's ROI (the tiles of the march): the ray of every held primary sample (its slot) cycles through
 // the parts home, home + 1, ... (mod n), multiplying its transmittance by
 // each one's.  A lane takes every kShadowSplit-th held sample of its pixel
 // (from its wavefront's place in the kShadowSplit of its tile), so that a wavefront's 64 rays start at the same depth
@@ -605,7 +604,7 @@ __global__ __launch_bounds__(256, 5) void tet_shadow(TetFrameParams f) {
     const float tf_k = 255.0f / (f.tf.vmax - f.tf.vmin);
     const float tf_o = -f.tf.vmin * tf_k;
     int lx, ly;
-    const int j = tile_pixel(f, blockIdx.x, lx, ly);
+    const int j = tile_pixel(f, f.tile0 + (int)blockIdx.x, lx, ly);
     const TetPartK& home = const_entry(f.parts, j);
     const bool live = lx < home.roi_w && ly < home.roi_h;
     long long slot0 = 0, slots = 0;
@@ -695,14 +694,23 @@ __global__ __launch_bounds__(256) void tet_resolve(TetFrameParams f) {
 
 template <int kLocator>
 void launch_tet_stages(TetFrameParams p, int stages, hipStream_t stream) {
-    const dim3 tiles(p.total_tiles), one(64), threads(64 * kWaves);
-    if (p.total_tiles <= 0) return;
-    if (stages & kTetCount) hipLaunchKernelGGL((tet_march<kTetCount, kLocator>), tiles, one, 0, stream, p);
-    if (stages & kTetRecord) hipLaunchKernelGGL((tet_march<kTetRecord, kLocator>), tiles, one, 0, stream, p);
+    const dim3 one(64), threads(64 * kWaves);
+    auto pieces = [&](auto launch) {
+        for (p.tile0 = 0; p.tile0 < p.total_tiles; p.tile0 += kMaxLaunchTiles)
+            launch(min(p.total_tiles - p.tile0, kMaxLaunchTiles));
+    };
+    if (stages & kTetCount)
+        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetCount, kLocator>), dim3(n), one, 0, stream, p); });
+    if (stages & kTetRecord)
+        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetRecord, kLocator>), dim3(n), one, 0, stream, p); });
     if ((stages & kTetShadow) && p.total > 0)
-        hipLaunchKernelGGL(tet_shadow<kLocator>, dim3(p.total_tiles, kShadowSplit / 4), dim3(256), 0, stream, p);
-    if (stages & kTetMarch) hipLaunchKernelGGL((tet_march<kTetMarch, kLocator>), tiles, threads, 0, stream, p);
-    if (stages & kTetShaded) hipLaunchKernelGGL((tet_march<kTetShaded, kLocator>), tiles, threads, 0, stream, p);
+        pieces([&](int n) {
+            hipLaunchKernelGGL(tet_shadow<kLocator>, dim3(n, kShadowSplit / 4), dim3(256), 0, stream, p);
+        });
+    if (stages & kTetMarch)
+        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetMarch, kLocator>), dim3(n), threads, 0, stream, p); });
+    if (stages & kTetShaded)
+        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetShaded, kLocator>), dim3(n), threads, 0, stream, p); });
 }
 
 }  // namespace

@@ -55,3 +55,33 @@ def test_ray_queue_shadows():
         del r
     ref, _, _ = oracle.render_scene_shadowed(sc, LIGHT, AMBIENT, bg=BG, pixels=pix)
     assert np.max(np.abs(got - np.asarray(ref).reshape(got.shape))) <= 1e-5
+
+
+def test_tetrahedral_parts_with_and_without_shadows():
+    import paper_2501_01628_amd as dp
+    cells = (2, 2, 2)
+    rng = np.random.default_rng(13)
+    v, t = synth.tet_mesh(cells, jitter=0.1, rng=rng)
+    vals = synth.tet_field(v, rng, cells)
+    cam = synth.inside_camera((0, 0, 0), cells, SIZE, SIZE)
+    pix = _pixels()
+    tf, vr, scale, dt = synth.hidden_tf(11), (0.02, 0.95), 0.7, 0.45
+    print("tets at 32768 x 32768", flush=True)
+    r = dp.TetRenderer([(v, t)], tf, vr, scale, dt, max_runs=1)
+    try:
+        r.set_values(0, vals)
+        r.set_camera(cam)
+        r.render(BG)
+        r.synchronize()
+        plain = _at(r.frame, pix)
+        assert r.shadow_plan() > SIZE * SIZE // 2
+        r.render_shadowed(LIGHT, AMBIENT, BG)
+        r.synchronize()
+        shadowed = _at(r.frame, pix)
+    finally:
+        r.close()
+        del r
+    ref, _ = oracle.render_tets(cam, [(v, vals, t)], tf, vr, scale, dt, BG, pixels=pix)
+    assert np.max(np.abs(plain - np.asarray(ref).reshape(plain.shape))) <= 1e-5
+    ref, _ = oracle.render_tets_shadowed(cam, [(v, vals, t)], tf, vr, scale, dt, LIGHT, AMBIENT, BG, pixels=pix)
+    assert np.max(np.abs(shadowed - np.asarray(ref).reshape(shadowed.shape))) <= 1e-5
