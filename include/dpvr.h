@@ -221,15 +221,15 @@ vr_status vr_set_render_params(vr_context ctx, double dt, float ert_epsilon);
 /* Launch path of the forward march; every path computes bit-identical
  * images (the sample positions and values do not depend on it):
  *   VR_PATH_STAGED  a workgroup per 16x16 pixel tile stages each slab of
- *                   brick slices its rays cross through LDS (default;
- *                   vr_render_partials takes the direct march instead for
- *                   bricks of a storage precision whose vr_set_march_config
- *                   was not called, where that is the faster one: few tiles,
- *                   small bricks, or float32 bricks seen at few voxels a
- *                   pixel);
+ *                   brick slices its rays cross through LDS;
  *   VR_PATH_DIRECT  every lane reads its voxels from HBM (vr_render_partials:
  *                   the same persistent work queue; vr_render_partial: one
- *                   wavefront per 8x8 tile). */
+ *                   wavefront per 8x8 tile).
+ * Until one is set, frames and batches are staged, and their bricks of a
+ * storage precision whose vr_set_march_config was not called either march
+ * directly where that is the faster one (few tiles, small bricks, or float32
+ * bricks seen at few voxels a pixel).  A batch takes VR_PATH_STAGED from the
+ * context it is created in, VR_PATH_DIRECT never. */
 typedef enum { VR_PATH_STAGED = 0, VR_PATH_DIRECT = 1 } vr_path;
 vr_status vr_set_march_path(vr_context ctx, vr_path path);
 
@@ -410,8 +410,9 @@ vr_status vr_batch_autotune(vr_batch batch, int32_t reps, double* best_ms);
  * (0 = as given, 1 = grouped by brick), staged family (vr_staging), tile
  * width and chunk length.  Any pointer may be NULL.  A new batch starts with
  * the context's march configuration and the most workgroups per CU that fit;
- * the bricks of a storage precision whose vr_set_march_config was not called
- * are marched directly (VR_PATH_DIRECT) where that is the faster one. */
+ * unless VR_PATH_STAGED was set, the bricks of a storage precision whose
+ * vr_set_march_config was not called are marched directly where that is the
+ * faster one. */
 vr_status vr_batch_config(vr_batch batch, int32_t* wg_per_cu, int32_t* order, int32_t* staging,
                           int32_t* tile_width, int32_t* chunk_slices);
 

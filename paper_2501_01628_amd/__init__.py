@@ -780,7 +780,10 @@ class Renderer:
     """Owns the torch buffers of one scene on one device and issues the
     C-ABI calls of a frame.  ``bricks`` is a list of (voxels, lo) with voxels a
     ghost-padded float32 array (numpy or torch, (nz+2, ny+2, nx+2)) and lo
-    the owned box's integer min corner; spacing is 1 (voxel units)."""
+    the owned box's integer min corner; spacing is 1 (voxel units).  With the
+    default path the library chooses the march of a frame;
+    ``vr_set_march_path(r.ctx, VR_PATH_STAGED)`` or a march_config make it the
+    staged one."""
 
     def __init__(self, bricks, tf, vrange=(0.0, 1.0), opacity_scale=1.0, dt=0.5,
                  ert_eps=2.0 ** -20, storage=VR_F32, device=0, stream=None, spacing=(1.0, 1.0, 1.0),
@@ -795,7 +798,8 @@ class Renderer:
         self.tf = torch.as_tensor(np.ascontiguousarray(tf, dtype=np.float32)).to(self.device)
         vr_set_transfer_function(self.ctx, self.tf, TF_ENTRIES, vrange[0], vrange[1], opacity_scale)
         vr_set_render_params(self.ctx, dt, ert_eps)
-        vr_set_march_path(self.ctx, path)
+        if path != VR_PATH_STAGED:
+            vr_set_march_path(self.ctx, path)
         if march_config is not None:     # (staging, tile_width, chunk_slices) for both storages
             for st in (VR_F32, VR_F16):
                 vr_set_march_config(self.ctx, st, *march_config)

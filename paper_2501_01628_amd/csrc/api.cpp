@@ -50,6 +50,7 @@ struct vr_context_s {
     double dt = 0.5;
     float ert_eps = 0x1p-20f;
     int32_t path = kPathStaged;
+    bool path_chosen = false;              // set by vr_set_march_path
     int32_t live_bricks = 0;
     int32_t live_tetparts = 0;
     int32_t tet_locator = kTetGrid;   // structure searched after the walk (vr_set_tet_locator)
@@ -534,6 +535,7 @@ vr_status vr_set_march_path(vr_context ctx, vr_path path) {
     if (path != VR_PATH_STAGED && path != VR_PATH_DIRECT)
         return fail(ctx, VR_ERR_INVALID_ARG, "vr_set_march_path: unknown path %d", (int)path);
     ctx->path = path == VR_PATH_DIRECT ? kPathDirect : kPathStaged;
+    ctx->path_chosen = true;
     return ok(ctx);
 }
 
@@ -786,11 +788,16 @@ struct DirectRule {
     }
 };
 
-// ... for a frame with the context's path; a staged configuration that the
-// caller chose is taken as it is.
+// Whether the caller chose the staged march for a storage group, by its path
+// or by its configuration: it is taken as it is.
+static bool chose_staged(vr_context ctx, int g) {
+    return ctx->cfg_chosen[g] || (ctx->path_chosen && ctx->path == kPathStaged);
+}
+
+// ... for a frame with the context's path.
 static bool frame_direct(vr_context ctx, int g, const MarchParams* jobs, int n) {
     if (ctx->path == kPathDirect) return true;
-    if (ctx->cfg_chosen[g]) return false;
+    if (chose_staged(ctx, g)) return false;
     DirectRule rule(g, ctx->cus);
     for (int i = 0; i < n; ++i) rule.add(jobs[i]);
     return rule.direct();
@@ -2713,7 +2720,7 @@ static vr_status batch_create(vr_context ctx, int32_t n_cameras, const vr_camera
                 rule.add(b->jobs[i]);
                 any = true;
             }
-        b->direct_pays[g2] = any && !ctx->cfg_chosen[g2] && rule.direct();
+        b->direct_pays[g2] = any && !chose_staged(ctx, g2) && rule.direct();
     }
     const long long n16 = std::count(b->f16.begin(), b->f16.end(), 1);
     const MarchCfg& mc = ctx->cfg[n16 > (long long)b->f16.size() - n16 ? 1 : 0];

@@ -1,0 +1,169 @@
+// Which march the library's host code gives a frame or a batch: the queue
+// launches of the host-memory HIP stand-in are recorded, and scenes on either
+// side of every line of the rule checked.
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "dpvr.h"
+#include "dpvr_kernels.h"
+
+// the stand-in's queue launcher under another name, so that this one can look
+// at the launches it checks
+#define launch_march_queue launch_march_queue_checked
+namespace dpvr {
+hipError_t launch_march_queue_checked(const QueueParams& q, StorageK storage, int workgroups, hipStream_t stream);
+}
+#include "fake_hip.cpp"
+#undef launch_march_queue
+
+static std::vector<int> g_staged[2];       // per storage: the launches' staged flags
+namespace dpvr {
+hipError_t launch_march_queue(const QueueParams& q, StorageK storage, int workgroups, hipStream_t stream) {
+    g_staged[storage == kF16 ? 1 : 0].push_back(q.staged);
+    return launch_march_queue_checked(q, storage, workgroups, stream);
+}
+}  // namespace dpvr
+
+static int g_fail = 0;
+#define EXPECT(cond)                                                             \
+    do {                                                                         \
+        if (!(cond)) {                                                           \
+            std::printf("FAILED line %d: %s\n", __LINE__, #cond);               \
+            ++g_fail;                                                            \
+        }                                                                        \
+    } while (0)
+
+static void* buf(size_t bytes) {
+    void* p = nullptr;
+    if (posix_memalign(&p, 256, bytes ? bytes : 256) != 0) std::abort();
+    return p;
+}
+
+// A grid of count[0] x count[1] x count[2] bricks of ext voxels each, seen from twice its
+// longest edge (az, el in degrees, 45 degrees high) by an image 4/3 as wide as
+// high.  The stand-in touches neither voxels nor images, so every brick and
+// partial shares one small buffer.
+struct Scene {
+    int32_t ext[3], count[3];
+    double step;
+    int f16, height;
+    double az = 30.0, el = 20.0;
+};
+
+struct Setup {
+    vr_context ctx = nullptr;
+    std::vector<vr_brick> bricks;
+    std::vector<vr_partial> parts;
+    void* ws;
+    void* img;
+    vr_camera_desc cam{};
+
+    explicit Setup(const Scene& s) {
+        EXPECT(vr_context_create(0, nullptr, &ctx) == VR_OK);
+        img = buf(4096);
+        EXPECT(vr_set_transfer_function(ctx, static_cast<float*>(img), DPVR_TF_ENTRIES, 0.f, 1.f, 1.f) == VR_OK);
+        EXPECT(vr_set_render_params(ctx, s.step, 0.f) == VR_OK);
+        double dims[3], top = 0.0;
+        for (int c = 0; c < 3; ++c) top = std::fmax(top, dims[c] = (double)s.ext[c] * s.count[c]);
+        const double pi = std::acos(-1.0), a = s.az * pi / 180.0, e = s.el * pi / 180.0;
+        const double off[3] = {std::cos(e) * std::sin(a), std::sin(e), std::cos(e) * std::cos(a)};
+        double eye[3], tgt[3];
+        const double up[3] = {0, 1, 0};
+        for (int c = 0; c < 3; ++c) {
+            tgt[c] = 0.5 * dims[c];
+            eye[c] = tgt[c] + 2.0 * top * off[c];
+        }
+        EXPECT(vr_set_camera_perspective(ctx, eye, tgt, up, 45.0, s.height * 4 / 3, s.height) == VR_OK);
+        cam.kind = 0;
+        for (int c = 0; c < 3; ++c) {
+            cam.eye[c] = eye[c];
+            cam.target[c] = tgt[c];
+            cam.up[c] = up[c];
+        }
+        cam.fovy_deg = 45.0;
+        cam.width = s.height * 4 / 3;
+        cam.height = s.height;
+        const double sp[3] = {1, 1, 1};
+        size_t bytes = 0;
+        EXPECT(vr_brick_workspace_size(s.ext, 1, s.f16 ? VR_F16 : VR_F32, &bytes) == VR_OK);
+        for (int k = 0; k < s.count[2]; ++k)
+            for (int j = 0; j < s.count[1]; ++j)
+                for (int i = 0; i < s.count[0]; ++i) {
+                    const double lo[3] = {(double)i * s.ext[0], (double)j * s.ext[1], (double)k * s.ext[2]};
+                    vr_brick b = nullptr;
+                    EXPECT(vr_brick_create(ctx, s.ext, 1, lo, sp, s.f16 ? VR_F16 : VR_F32, img, bytes, &b) == VR_OK);
+                    EXPECT(vr_brick_set_data(b, static_cast<float*>(img)) == VR_OK);
+                    bricks.push_back(b);
+                    int32_t r[4];
+                    EXPECT(vr_partial_roi(ctx, b, r) == VR_OK);
+                    parts.push_back(vr_partial{r[0], r[1], r[2], r[3], static_cast<float*>(img),
+                                               static_cast<float*>(img), nullptr});
+                }
+        EXPECT(vr_frame_workspace_size((int32_t)bricks.size(), &bytes) == VR_OK);
+        ws = buf(bytes);
+    }
+    ~Setup() {
+        for (vr_brick b : bricks) EXPECT(vr_brick_release(b) == VR_OK);
+        EXPECT(vr_context_release(ctx) == VR_OK);
+        std::free(ws);
+        std::free(img);
+    }
+    // 1 staged, 0 direct
+    int frame(int f16) {
+        g_staged[0].clear();
+        g_staged[1].clear();
+        size_t bytes = 0;
+        EXPECT(vr_frame_workspace_size((int32_t)bricks.size(), &bytes) == VR_OK);
+        EXPECT(vr_render_partials(ctx, (int32_t)bricks.size(), bricks.data(), parts.data(), ws, bytes) == VR_OK);
+        EXPECT(g_staged[f16].size() == 1 && g_staged[1 - f16].empty());
+        return g_staged[f16].empty() ? -1 : g_staged[f16][0];
+    }
+    int batch(int f16) {
+        g_staged[0].clear();
+        g_staged[1].clear();
+        const vr_tf_desc tf{static_cast<float*>(img), 0.f, 1.f, 1.f, 0};
+        std::vector<vr_batch_job> jobs;
+        for (size_t i = 0; i < bricks.size(); ++i) jobs.push_back(vr_batch_job{bricks[i], 0, 0, parts[i]});
+        size_t bytes = 0;
+        EXPECT(vr_batch_workspace_size((int32_t)jobs.size(), 0, &bytes) == VR_OK);
+        void* bws = buf(bytes);
+        vr_batch b = nullptr;
+        EXPECT(vr_batch_create(ctx, 1, &cam, 1, &tf, (int32_t)jobs.size(), jobs.data(), 0, nullptr, bws, bytes, &b) ==
+               VR_OK);
+        const int r = g_staged[f16].empty() ? -1 : g_staged[f16].back();
+        if (b) EXPECT(vr_batch_release(b) == VR_OK);
+        std::free(bws);
+        return r;
+    }
+};
+
+int main() {
+    // a frame of few tiles marches from HBM by default; a caller's choice of
+    // the staged march, as a path or as a configuration, is taken as it is
+    const Scene small{{64, 64, 64}, {1, 1, 1}, 0.5, 0, 160};
+    for (int f16 = 0; f16 < 2; ++f16) {
+        Scene s = small;
+        s.f16 = f16;
+        { Setup u(s); EXPECT(u.frame(f16) == 0 && u.batch(f16) == 0); }
+        {
+            Setup u(s);
+            EXPECT(vr_set_march_path(u.ctx, VR_PATH_STAGED) == VR_OK);
+            EXPECT(u.frame(f16) == 1 && u.batch(f16) == 1);
+            EXPECT(vr_set_march_path(u.ctx, VR_PATH_DIRECT) == VR_OK);
+            EXPECT(u.frame(f16) == 0);
+            EXPECT(vr_set_march_path(u.ctx, VR_PATH_STAGED) == VR_OK);
+            EXPECT(u.frame(f16) == 1);
+        }
+        {
+            Setup u(s);
+            EXPECT(vr_set_march_config(u.ctx, f16 ? VR_F16 : VR_F32, VR_STAGING_RING, 16, 8) == VR_OK);
+            EXPECT(u.frame(f16) == 1 && u.batch(f16) == 1);
+            EXPECT(vr_set_march_path(u.ctx, VR_PATH_DIRECT) == VR_OK);
+            EXPECT(u.frame(f16) == 0);
+        }
+    }
+    std::printf("%s: %d failed expectations\n", g_fail ? "FAIL" : "OK", g_fail);
+    return g_fail ? 1 : 0;
+}
