@@ -729,41 +729,50 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
 // Whether a queue of jobs of one storage precision (g: 0 float32, 1 float16)
 // is faster marched from HBM than staged; every path gives the same bits.
 // Staging pays by the samples that a staged voxel serves and needs a
-// workgroup's LDS for each tile, so the direct march is the faster one
+// workgroup's LDS for each tile; the direct march pays by the cache lines that
+// its rays share.  Every figure below is staged over direct time.  Direct is
+// the faster one
 // * when the tiles are few (2 per CU; 1.4 for float16 below half a voxel a
 //   step): a staged workgroup then walks the slabs of one tile alone, and the
-//   frame lasts as long as one
-//   (step 0.5, staged and direct: 64^3 at 283x212, 210 tiles, 98 and 68 us,
-//   float16 76 and 64; 160^3 at 353x265, 388 tiles, 203 and 155, float16 188
-//   and 172; 320^3 at 353x265, 503 tiles, 491 and 395, float16 504 and 300;
-//   160^3 at 441x331, 608 tiles, 190 and 183, float16 178 and 195; step 0.25,
-//   160^3 float16 at 415x311, 505 tiles, 277 and 292);
+//   frame lasts as long as one (step 0.5: one brick of 64^3 to 400^3 at 36 to
+//   506 tiles 1.0 to 2.8, float16 0.9 to 3.4; 160^3 at 608 tiles 1.04, float16
+//   0.91; step 0.25, 160^3 float16 at 505 tiles 0.95) -- unless they are more
+//   than one per CU from many bricks of 1 MB and more at more than 5.4 voxels a
+//   pixel (294 to 500 tiles at 6.2 to 7.5 at the centre: 64 to 216 bricks of 1.2 MB 0.70 to
+//   0.92, of 4 and 8 MB 0.70 to 0.97, of 32 MB 0.86; of 0.5 to 0.95 MB 1.5 to 2.0; at
+//   5.5 1.23; 27 bricks of 32 MB on 158 tiles at 10.4 1.6);
 // * for float32 bricks seen at few voxels a pixel, where the lanes of a
-//   wavefront share the lines they read, up to sqrt(1.28 step) voxels a pixel
-//   with the step in voxels: a coarse step has fewer samples per staged voxel
-//   (step 0.5, line at 0.8: 512^3 at 0.5 voxels a pixel 4.05 ms staged and 3.13
-//   direct, at 0.8 0.98 to 1.17 times as fast, at 1.0 1.26 ms and 1.40; step
-//   0.25, line at 0.57, 320^3: at 0.5 1.93 and 1.76, at 0.75 1.01 and 1.05;
-//   step 1, line at 1.13: at 1.0 339 us and 302, at 1.4 315 and 335).  float16
-//   bricks stage twice the voxels in the same LDS: direct is 0.64 to 1.04 times
-//   as fast there;
-// * for small bricks, whose voxels stay in the caches: float32 bricks that fit
-//   an XCD's 4 MB L2, or twice that up to 1.6 of the line above, and float16
-//   ones up to 8 MB from one voxel a pixel on, where few samples share a staged
-//   voxel (batches of 12 frames of 8 bricks at 512x512: of 24 to 64 voxels an
-//   edge 341 us staged and 239 direct, float16 243 and 227; of 48 to 160, 5 to 8
-//   MB a tile, 742 and 718, float16 639 and 494; the latter at 256x256, 4.6
-//   voxels a pixel, 441 and 451, at 1024x1024, 1.1 a pixel, 733 and 582; of 160
-//   to 256, 36 MB, at 384x384 2.03 ms and 2.75, float16 1.25 and 1.51; frames of
-//   320^3 in 27 bricks, 5 to 8 MB, at 1.0 voxels a pixel 1.06 to 1.25 times as
-//   fast, at 1.4 and 2.0 0.89 to 1.23).
+//   wavefront share the lines they read: up to sqrt(1.28 step) voxels a pixel
+//   with the step in voxels, since a coarse step has fewer samples per staged
+//   voxel, and up to 0.75 (20 MB / brick)^(1/4), since the lines of a large
+//   brick that the rays of a tile cross are in no cache any more (six views of
+//   seven volumes in 1, 8 and 24 bricks, the worst view and the best: bricks of
+//   6 and 11 MB at 0.8, step 0.5, 1.05 and 1.74, at 1.1, step 1, 0.97 and 1.5; of
+//   17 to 23 MB at 0.6 1.01 and 1.65, at 0.8 0.79 and 1.66, at 1.1 0.79 and 1.55;
+//   of 33 to 70 MB at 0.57, step 1, 0.98 and 1.9, at 0.8 0.75 and 1.5; of 125 to
+//   260 MB at 0.4 0.88 and 1.5, at 0.8 0.75 and 1.3; of 456 to 990 MB at 0.4 0.82
+//   and 1.5, at 0.8 0.68 and 1.5).  float16 bricks stage twice the voxels in the
+//   same LDS: direct is 0.64 to 1.04 times as fast there;
+// * for small bricks, whose voxels stay in the caches.  float32: of up to 4 MB
+//   (an XCD's L2) while brick x (voxels a pixel)^2, the bytes that a pixel's
+//   surroundings span, is below 7 MB (216 to 512 bricks, steps 0.25 to 1: of 0.16
+//   MB at 0.8 to 7.4 voxels a pixel 1.11 to 2.3; of 0.5 MB at 2.2 1.06 to 1.2, at
+//   3 1.0, at 5.5 0.74 to 1.1; of 1.2 MB at 2.2 1.13 to 1.2, at 3 0.89 to 1.03,
+//   at 4 0.70 to 0.8; of 2.2 MB at 1.6 1.07 to 1.17, at 2.2 0.91 to 1.02, at 4
+//   0.81 to 0.86), and of twice that up to 1.6 of the line above (4.2 MB at 1.2,
+//   step 0.5, 1.25; 8 MB at 1.0, step 0.5, 1.1).  float16: up to 8 MB from one
+//   voxel a pixel on, where few samples share a staged voxel (0.08 to 4 MB at 1.2
+//   to 7.5 voxels a pixel, steps 0.5 and 1, 0.95 to 2.1; of 8.2 MB at 4 0.85), at
+//   a step below half a voxel up to 3 MB and 30 MB of brick x (voxels a pixel)^2
+//   (step 0.25: of 0.6 MB at 4 1.4, at 5.5 and 7.5 0.98; of 1.1 MB at 4 1.3, at
+//   7.5 0.73; of 2.1 MB at 3 1.12, at 4 0.90; of 4 MB at 1.2 to 1.6 0.85 to 0.89).
 struct DirectRule {
     int g, cus;
     // sums weighted by a job's tiles: voxels a pixel at the brick's centre,
     // the same over the line, bytes of the brick
     double tiles = 0.0, pixel = 0.0, line = 0.0, bytes = 0.0;
-    bool few2;
-    DirectRule(int group, int cu_count) : g(group), cus(cu_count), few2(group == 0) {}
+    bool coarse;                 // float32, or a float16 job at half a voxel a step or more
+    DirectRule(int group, int cu_count) : g(group), cus(cu_count), coarse(group == 0) {}
     void add(const MarchParams& p) {
         const CameraK& c = p.cam;
         const BrickK& b = p.brick;
@@ -775,16 +784,19 @@ struct DirectRule {
         }
         const double fine = std::min(b.spacing[0], std::min(b.spacing[1], b.spacing[2]));
         const double vpp = std::fabs(depth) * 2.0 * c.ay / ((double)c.height * fine);
-        few2 = few2 || 2.0 * p.dt >= fine;
+        const double size = (g == 0 ? 4.0 : 2.0) * b.sdim[0] * b.sdim[1] * b.sdim[2];
+        coarse = coarse || 2.0 * p.dt >= fine;
         tiles += t;
         pixel += t * vpp;
-        line += t * vpp / std::sqrt(1.28 * p.dt / fine);
-        bytes += t * (g == 0 ? 4.0 : 2.0) * b.sdim[0] * b.sdim[1] * b.sdim[2];
+        line += t * vpp / std::min(std::sqrt(1.28 * p.dt / fine), 0.75 * std::pow(20.0e6 / size, 0.25));
+        bytes += t * size;
     }
     bool direct() const {
-        if (tiles <= (few2 ? 2.0 : 1.4) * cus) return true;
-        if (g == 1) return pixel >= tiles && bytes <= 8.0e6 * tiles;
-        return line <= tiles || bytes <= 4.0e6 * tiles || (bytes <= 8.0e6 * tiles && line <= 1.6 * tiles);
+        if (tiles <= 0.0) return true;
+        const double v = pixel / tiles, l = line / tiles, b = bytes / tiles;
+        if (tiles <= (coarse ? 2.0 : 1.4) * cus && (tiles <= cus || v <= 5.4 || b <= 1.0e6)) return true;
+        if (g == 1) return v >= 1.0 && b <= 8.0e6 && (coarse || (b <= 3.0e6 && b * v * v <= 30.0e6));
+        return l <= 1.0 || (b <= 4.0e6 && b * v * v <= 7.0e6) || (b <= 8.0e6 && l <= 1.6);
     }
 };
 

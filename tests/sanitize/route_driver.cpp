@@ -164,6 +164,50 @@ int main() {
             EXPECT(u.frame(f16) == 0);
         }
     }
+    // on either side of the rule's lines (voxels a pixel in brackets)
+    const struct {
+        Scene s;
+        int staged;
+    } lines[] = {
+        {{{200, 200, 200}, {1, 1, 1}, 0.5, 0, 400}, 0},              // 506 tiles of one brick
+        {{{200, 200, 200}, {3, 3, 3}, 0.5, 0, 96}, 0},               // 158 tiles, 32 MB bricks [10.4]
+        {{{200, 200, 200}, {3, 3, 3}, 0.5, 0, 160}, 1},              // 347 tiles [6.2]
+        {{{100, 100, 100}, {5, 5, 5}, 0.5, 0, 110}, 1},              // 500 tiles, 4 MB bricks [7.5]
+        {{{48, 48, 48}, {7, 7, 7}, 0.5, 0, 74}, 0},                  // 362 tiles, 0.5 MB bricks [7.5]
+        {{{32, 32, 32}, {8, 8, 8}, 0.25, 0, 106}, 0},                // 919 tiles, 0.16 MB bricks [4.0]
+        {{{64, 64, 64}, {6, 6, 6}, 0.5, 0, 289}, 0},                 // 1.2 MB bricks [2.2]
+        {{{64, 64, 64}, {6, 6, 6}, 0.25, 0, 212}, 1},                // [3.0]
+        {{{64, 64, 64}, {6, 6, 6}, 0.5, 0, 116}, 1},                 // [5.5]
+        {{{80, 80, 80}, {6, 6, 6}, 0.5, 0, 497}, 0},                 // 2.2 MB bricks [1.6]
+        {{{80, 80, 80}, {6, 6, 6}, 0.5, 0, 199}, 1},                 // [4.0]
+        {{{100, 100, 100}, {5, 5, 5}, 0.5, 0, 690}, 0},              // 4.2 MB bricks [1.2]
+        {{{100, 100, 100}, {5, 5, 5}, 0.5, 0, 376}, 1},              // [2.2]
+        {{{192, 192, 128}, {2, 2, 2}, 0.5, 0, 1080}, 0},             // 19 MB bricks [0.59]
+        {{{256, 256, 256}, {2, 2, 2}, 0.5, 0, 1082}, 1},             // 69 MB bricks [0.78]
+        {{{256, 256, 256}, {2, 2, 2}, 0.5, 0, 2120}, 0},             // [0.4]
+        {{{250, 900, 500}, {1, 1, 1}, 1.0, 0, 1345}, 1},             // 456 MB [1.11]
+        {{{250, 900, 500}, {1, 1, 1}, 0.5, 0, 2485}, 1},             // [0.6]
+        {{{2300, 1100, 40}, {1, 1, 1}, 1.0, 0, 3432}, 1},            // slices of 10 MB [1.11]
+        {{{256, 512, 256}, {4, 2, 2}, 0.5, 0, 1080}, 1},             // 16 bricks of 1024 x 1024 x 512 at full HD
+        {{{128, 128, 128}, {2, 2, 2}, 0.5, 0, 2000, 100.0, 20.0}, 0},
+        {{{64, 64, 64}, {6, 6, 6}, 0.5, 1, 397}, 0},                 // float16, 0.6 MB bricks [1.6]
+        {{{64, 64, 64}, {6, 6, 6}, 0.5, 1, 800}, 1},                 // [0.8]
+        {{{125, 125, 125}, {4, 4, 4}, 0.5, 1, 376}, 0},              // 4.1 MB bricks [2.2]
+        {{{125, 125, 125}, {4, 4, 4}, 0.25, 1, 517}, 1},             // [1.6]
+        {{{80, 80, 80}, {6, 6, 6}, 0.25, 1, 199}, 0},                // 1.1 MB bricks [4.0]
+        {{{80, 80, 80}, {6, 6, 6}, 0.25, 1, 106}, 1},                // [7.5]
+        {{{158, 158, 158}, {4, 4, 4}, 0.5, 1, 475}, 1},              // 8.2 MB bricks [2.2]
+    };
+    for (const auto& c : lines) {
+        Setup u(c.s);
+        const int frame = u.frame(c.s.f16), batch = u.batch(c.s.f16);
+        if (frame != c.staged || batch != c.staged) {
+            std::printf("FAILED: %d x %d x %d in %d bricks of an axis, step %g, storage %d, height %d: frame %d, batch "
+                        "%d, expected %d\n", c.s.ext[0], c.s.ext[1], c.s.ext[2], c.s.count[0], c.s.step, c.s.f16,
+                        c.s.height, frame, batch, c.staged);
+            ++g_fail;
+        }
+    }
     std::printf("%s: %d failed expectations\n", g_fail ? "FAIL" : "OK", g_fail);
     return g_fail ? 1 : 0;
 }
