@@ -2147,6 +2147,28 @@ struct TetShadowArgs {
     int64_t* total_out = nullptr;
 };
 
+// Whether a frame's tiles take a wavefront each rather than a workgroup whose
+// wavefronts share their rays: a workgroup a tile costs 3 ns of the GPU however
+// little its rays hold, a wavefront alone waits for the slowest of its rays.
+// A wavefront is the better one for many tiles: from 28000 on, and from 10000 on
+// with at most 5 samples across a part (workgroup over wavefront time, samples
+// across a part falling from 85 or more to 1: 6400 tiles 0.63 to 1.3, 14000 0.67
+// to 1.4, there at 5 and fewer 0.95 to 1.3; 25000 0.75 to 1.2, at 5 and fewer 1.1
+// to 1.6; 30000 1.03 to 1.5; 56000 0.98 to 2.3.  24^3 cells in 10 parts at
+// 1280x720, 3 samples across: 269 and 183 us, 172 when a workgroup took four
+// tiles in step).
+static bool tet_alone(int32_t n, const vr_tetpart* parts, const std::vector<int32_t>& prefix, double dt) {
+    double across = 0.0;
+    const double tiles = prefix[n];
+    for (int i = 0; i < n; ++i) {
+        const TetTables& t = parts[i]->tab;
+        double e = 0.0;
+        for (int c = 0; c < 3; ++c) e = std::max(e, t.hi[c] - t.lo[c]);
+        if (prefix[i + 1] > prefix[i]) across += (prefix[i + 1] - prefix[i]) * (e / dt);
+    }
+    return tiles >= 28000.0 || (tiles >= 10000.0 && across <= 5.0 * tiles);
+}
+
 // The frame of n parts, `stages` a mask of the kTet* stages (march into the
 // workspace's run buffers, resolve into out; with `sh`: count + scan into
 // the plan, or record + shadow steps + shaded march).
@@ -2248,6 +2270,7 @@ static vr_status tet_frame(vr_context ctx, int32_t n, const vr_tetpart* parts, i
     f.samples = samples;
     f.err = err_word(ctx);
     f.locator = ctx->tet_locator;
+    f.alone = tet_alone(n, parts, prefix, ctx->dt) ? 1 : 0;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, VR_ERR_DEVICE, "%s: cannot select device %d", who, ctx->device);
     hipError_t e = hipSuccess;

@@ -46,6 +46,7 @@ struct TetFrameParams {
     const int32_t* tile_start;  // device, n + 1: exclusive prefix of tiles (tet_tiles)
     int32_t n, total_tiles, max_runs;
     int32_t tile0;              // first tile of a launch
+    int32_t alone;              // marches into runs: 1 a wavefront a tile, 0 a workgroup a tile
     int32_t width, height;
     float bg[4];
     float* out;                 // height x width x 4

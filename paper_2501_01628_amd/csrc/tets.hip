@@ -356,7 +356,10 @@ __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, do
 // too few tiles to fill the GPU.  (One fixed stretch per wavefront leaves most
 // of them idle: a part fills its bounding box unevenly.)  The stretches' runs
 // wait in a pool of kPool entries in LDS, chained per ray and stretch, and are
-// joined in order afterwards.
+// joined in order afterwards.  (A tile that needs more is taken again by one
+// wavefront: 32 layers of cells in turn from two parts, 16 runs a ray and part,
+// 2.95 ms, 2.36 with one lane a ray in step; 16 layers fit, 0.38 and 1.07 ms.
+// Four wavefronts taking 16 rays each: 2.73, but 48 layers 4.43 against 4.28.)
 constexpr int kWaves = 4;
 constexpr int kStretches = 8;
 constexpr int kPool = 704;
@@ -393,28 +396,32 @@ __device__ inline int tile_pixel(const TetFrameParams& f, int wg, int& lx, int& 
 template <int kMode>
 constexpr bool tet_runs() { return kMode == kTetMarch || kMode == kTetShaded; }
 
-template <int kMode, int kLocator>
+// kAlone: every wavefront takes a tile of its own, its rays whole (api.cpp's
+// tet_alone chooses).
+template <int kMode, int kLocator, bool kAlone>
 __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_march(TetFrameParams f) {
     constexpr bool kRuns = tet_runs<kMode>();
+    constexpr bool kPooled = kRuns && !kAlone;
     __shared__ TFTable tft;
-    __shared__ int run_key[kRuns ? kPool : 1], run_end[kRuns ? kPool : 1];
-    __shared__ float run_rgb[kRuns ? 3 * kPool : 1], run_T[kRuns ? kPool : 1];
-    __shared__ short run_next[kRuns ? kPool : 1];
-    __shared__ short first_run[kRuns ? kStretches * 64 : 1];
+    __shared__ int run_key[kPooled ? kPool : 1], run_end[kPooled ? kPool : 1];
+    __shared__ float run_rgb[kPooled ? 3 * kPool : 1], run_T[kPooled ? kPool : 1];
+    __shared__ short run_next[kPooled ? kPool : 1];
+    __shared__ short first_run[kPooled ? kStretches * 64 : 1];
     __shared__ int pool_used, taken;
     const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
     if (kRuns) {
         load_tf(tft, f.tf, f.dt, threadIdx.x, 64 * kWaves);
-        if (threadIdx.x == 0) {
+        if (kPooled && threadIdx.x == 0) {
             pool_used = 0;
             taken = kWaves;
         }
         __syncthreads();
     }
     int lx, ly;
-    const int j = tile_pixel(f, f.tile0 + (int)blockIdx.x, lx, ly);
+    const int tile = f.tile0 + (kRuns && kAlone ? kWaves * (int)blockIdx.x + wave : (int)blockIdx.x);
+    const int j = tile_pixel(f, min(tile, f.total_tiles - 1), lx, ly);
     const TetPartK& P = const_entry(f.parts, j);
-    const bool live = lx < P.roi_w && ly < P.roi_h;
+    const bool live = lx < P.roi_w && ly < P.roi_h && tile < f.total_tiles;
     const long long npix = (long long)P.roi_w * P.roi_h;
     const long long li = (long long)ly * P.roi_w + lx;
     const float tf_k = 255.0f / (f.tf.vmax - f.tf.vmin);
@@ -459,7 +466,7 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
     // the stretches of this wavefront; should the pool not hold the tile's
     // runs, wavefront 0 takes its rays again, whole, and stores their runs as
     // they end
-    bool whole = false;
+    bool whole = kAlone;
     for (int piece = wave;;) {
         const long long n = k1 - k0 + 1;
         long long ka = k0 + n * piece / kStretches, kb = k0 + n * (piece + 1) / kStretches - 1;
@@ -532,7 +539,7 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
         });
         if (in_run) close_run();
         counted += held;
-        if (whole) break;
+        if (kAlone || whole) break;
         first_run[piece * 64 + lane] = (short)first;
         if (lane == 0) piece = atomicAdd(&taken, 1);
         piece = uniform_i(piece);
@@ -542,8 +549,8 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
         if (!whole || wave > 0) break;
         counted = 0;
     }
-    if (whole && wave > 0) counted = 0;
-    if (wave == 0 && live) {
+    if (!kAlone && whole && wave > 0) counted = 0;
+    if ((kAlone || wave == 0) && live) {
         if (!whole) {
             // join the stretches: a run that goes on in the next one is one run
             nrun = 0;
@@ -700,17 +707,21 @@ void launch_tet_stages(TetFrameParams p, int stages, hipStream_t stream) {
             launch(min(p.total_tiles - p.tile0, kMaxLaunchTiles));
     };
     if (stages & kTetCount)
-        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetCount, kLocator>), dim3(n), one, 0, stream, p); });
+        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetCount, kLocator, true>), dim3(n), one, 0, stream, p); });
     if (stages & kTetRecord)
-        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetRecord, kLocator>), dim3(n), one, 0, stream, p); });
+        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetRecord, kLocator, true>), dim3(n), one, 0, stream, p); });
     if ((stages & kTetShadow) && p.total > 0)
         pieces([&](int n) {
             hipLaunchKernelGGL(tet_shadow<kLocator>, dim3(n, kShadowSplit / 4), dim3(256), 0, stream, p);
         });
-    if (stages & kTetMarch)
-        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetMarch, kLocator>), dim3(n), threads, 0, stream, p); });
-    if (stages & kTetShaded)
-        pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetShaded, kLocator>), dim3(n), threads, 0, stream, p); });
+    auto runs = [&](auto pooled, auto alone) {
+        pieces([&](int n) {
+            if (p.alone) hipLaunchKernelGGL(alone, dim3((n + kWaves - 1) / kWaves), threads, 0, stream, p);
+            else hipLaunchKernelGGL(pooled, dim3(n), threads, 0, stream, p);
+        });
+    };
+    if (stages & kTetMarch) runs(tet_march<kTetMarch, kLocator, false>, tet_march<kTetMarch, kLocator, true>);
+    if (stages & kTetShaded) runs(tet_march<kTetShaded, kLocator, false>, tet_march<kTetShaded, kLocator, true>);
 }
 
 }  // namespace

@@ -8,18 +8,30 @@
 
 #include "dpvr.h"
 #include "dpvr_kernels.h"
+#include "tet_kernels.h"
 
-// the stand-in's queue launcher under another name, so that this one can look
-// at the launches it checks
+// the stand-in's queue and mesh launchers under other names, so that these can
+// look at the launches they check
 #define launch_march_queue launch_march_queue_checked
+#define launch_tet_frame launch_tet_frame_checked
 namespace dpvr {
 hipError_t launch_march_queue_checked(const QueueParams& q, StorageK storage, int workgroups, hipStream_t stream);
+hipError_t launch_tet_frame_checked(TetFrameParams f, int stages, hipStream_t stream);
 }
 #include "fake_hip.cpp"
 #undef launch_march_queue
+#undef launch_tet_frame
 
 static std::vector<int> g_staged[2];       // per storage: the launches' staged flags
+static int g_alone = -1, g_tet_tiles = 0;
 namespace dpvr {
+hipError_t launch_tet_frame(TetFrameParams f, int stages, hipStream_t stream) {
+    if (stages & kTetMarch) {
+        g_alone = f.alone;
+        g_tet_tiles = f.total_tiles;
+    }
+    return launch_tet_frame_checked(f, stages, stream);
+}
 hipError_t launch_march_queue(const QueueParams& q, StorageK storage, int workgroups, hipStream_t stream) {
     g_staged[storage == kF16 ? 1 : 0].push_back(q.staged);
     return launch_march_queue_checked(q, storage, workgroups, stream);
@@ -139,6 +151,50 @@ struct Setup {
     }
 };
 
+// A cube of one tetrahedron-filled cell per part, `copies` of it over each
+// other (each its own part), filling an image of the given size; 1 if a
+// wavefront takes a tile.
+static int tet_route(int copies, int width, int height, double dt, int* tiles) {
+    const double v[24] = {0, 0, 0, 0, 0, 1, 0, 1, 0, 0, 1, 1, 1, 0, 0, 1, 0, 1, 1, 1, 0, 1, 1, 1};
+    const int32_t t[24] = {0, 4, 6, 7, 0, 4, 5, 7, 0, 2, 6, 7, 0, 2, 3, 7, 0, 1, 5, 7, 0, 1, 3, 7};
+    vr_context ctx = nullptr;
+    EXPECT(vr_context_create(0, nullptr, &ctx) == VR_OK);
+    void* img = buf((size_t)16 * width * height);
+    EXPECT(vr_set_transfer_function(ctx, static_cast<float*>(img), DPVR_TF_ENTRIES, 0.f, 1.f, 1.f) == VR_OK);
+    EXPECT(vr_set_render_params(ctx, dt, 0.f) == VR_OK);
+    const double pos[3] = {0.5, 0.5, -1}, dir[3] = {0, 0, 1}, up[3] = {0, 1, 0};
+    EXPECT(vr_set_camera_orthographic(ctx, pos, dir, up, 0.5, width, height) == VR_OK);
+    std::vector<vr_tetpart> parts;
+    std::vector<void*> mem;
+    const float vals[8] = {};
+    for (int i = 0; i < copies; ++i) {
+        vr_tetpart q = nullptr;
+        EXPECT(vr_tetpart_create(ctx, v, 8, t, 6, &q) == VR_OK);
+        double lo[3], hi[3];
+        int32_t grid[3];
+        int64_t count;
+        size_t bytes = 0;
+        int32_t nt = 0;
+        EXPECT(vr_tetpart_info(q, lo, hi, grid, &count, &bytes, &nt) == VR_OK);
+        mem.push_back(buf(bytes));
+        EXPECT(vr_tetpart_attach(q, mem.back(), bytes) == VR_OK);
+        EXPECT(vr_tetpart_set_values(q, vals) == VR_OK);
+        parts.push_back(q);
+    }
+    size_t need = 0;
+    EXPECT(vr_tetparts_workspace_size(ctx, copies, parts.data(), 1, &need) == VR_OK);
+    mem.push_back(buf(need));
+    const float bg[4] = {0, 0, 0, 0};
+    EXPECT(vr_render_tetparts(ctx, copies, parts.data(), 1, bg, mem.back(), need, static_cast<float*>(img), nullptr) ==
+           VR_OK);
+    for (vr_tetpart q : parts) EXPECT(vr_tetpart_release(q) == VR_OK);
+    EXPECT(vr_context_release(ctx) == VR_OK);
+    for (void* p : mem) std::free(p);
+    std::free(img);
+    *tiles = g_tet_tiles;
+    return g_alone;
+}
+
 int main() {
     // a frame of few tiles marches from HBM by default; a caller's choice of
     // the staged march, as a path or as a configuration, is taken as it is
@@ -207,6 +263,15 @@ int main() {
                         c.s.height, frame, batch, c.staged);
             ++g_fail;
         }
+    }
+    // tetrahedral tiles by wavefront: many, or fewer with few samples across a part
+    {
+        int tiles = 0;
+        EXPECT(tet_route(1, 640, 640, 0.25, &tiles) == 0 && tiles == 6400);
+        EXPECT(tet_route(1, 800, 800, 0.25, &tiles) == 1 && tiles == 10000);
+        EXPECT(tet_route(1, 800, 800, 0.125, &tiles) == 0 && tiles == 10000);
+        EXPECT(tet_route(2, 904, 904, 0.01, &tiles) == 0 && tiles == 25538);
+        EXPECT(tet_route(3, 800, 800, 0.01, &tiles) == 1 && tiles == 30000);
     }
     std::printf("%s: %d failed expectations\n", g_fail ? "FAIL" : "OK", g_fail);
     return g_fail ? 1 : 0;
