@@ -38,6 +38,9 @@
 #include "march_common.h"
 #include "tet_kernels.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace dpvr {
 namespace {
 
@@ -596,12 +599,12 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
 
 // The shadow rays of one tile of a home part's ROI (the tiles of the march): the ray of every held primary sample (its slot) cycles through
 // the parts home, home + 1, ... (mod n), multiplying its transmittance by
-// each one's.  A lane takes every kShadowSplit-th held sample of its pixel
-// (from its wavefront's place in the kShadowSplit of its tile), so that a wavefront's 64 rays start at the same depth
+// each one's.  A lane takes every split-th held sample of its pixel (split: the
+// wavefronts of a tile, from its wavefront's place among them), so that a wavefront's 64 rays start at the same depth
 // behind 8 x 8 neighbouring pixels and cross the same tetrahedra; with the
 // lanes on 64 consecutive samples of one primary ray their loads touched as
 // many lines as lanes.
-constexpr int kShadowSplit = 256;
+constexpr int kMaxShadowSplit = 256;
 
 template <int kLocator>
 __global__ __launch_bounds__(256, 5) void tet_shadow(TetFrameParams f) {
@@ -623,7 +626,7 @@ __global__ __launch_bounds__(256, 5) void tet_shadow(TetFrameParams f) {
         cr = camera_ray(f.cam, home.roi_x0 + lx, home.roi_y0 + ly);
     }
     unsigned long long evaluated = 0;
-    for (long long i = 4 * blockIdx.y + (threadIdx.x >> 6); i < slots; i += kShadowSplit) {
+    for (long long i = 4 * blockIdx.y + (threadIdx.x >> 6); i < slots; i += 4 * gridDim.y) {
         CamRay sr;
         {
 #pragma clang fp contract(off)
@@ -699,6 +702,17 @@ __global__ __launch_bounds__(256) void tet_resolve(TetFrameParams f) {
         make_float4(fmaf(w, f.bg[0], C0), fmaf(w, f.bg[1], C1), fmaf(w, f.bg[2], C2), fmaf(w, f.bg[3], A));
 }
 
+// Wavefronts per tile of the shadow rays: 6 for each held sample of the ROIs'
+// mean pixel, at most kMaxShadowSplit (a lane past its pixel's samples only
+// loads the table, but a pixel may hold many times the mean).  Always 256, a
+// frame of short rays spent its time on workgroups without work: 16^3 cells in 4
+// parts at 800x600, step 8, 1571 us, 289 so; step 0.5 4.51 and 3.46 ms; 40^3 in 4
+// parts at 384x288, step 0.5, 5.48 and 5.45 (2.5 a sample: 5.66).
+int shadow_split(const TetFrameParams& p) {
+    const double mean = (double)p.total / ((double)kTetTile * kTetTile * p.total_tiles);
+    return 4 * (int)std::min(kMaxShadowSplit / 4.0, 1.0 + std::ceil(6.0 * mean / 4.0));
+}
+
 template <int kLocator>
 void launch_tet_stages(TetFrameParams p, int stages, hipStream_t stream) {
     const dim3 one(64), threads(64 * kWaves);
@@ -712,7 +726,7 @@ void launch_tet_stages(TetFrameParams p, int stages, hipStream_t stream) {
         pieces([&](int n) { hipLaunchKernelGGL((tet_march<kTetRecord, kLocator, true>), dim3(n), one, 0, stream, p); });
     if ((stages & kTetShadow) && p.total > 0)
         pieces([&](int n) {
-            hipLaunchKernelGGL(tet_shadow<kLocator>, dim3(n, kShadowSplit / 4), dim3(256), 0, stream, p);
+            hipLaunchKernelGGL(tet_shadow<kLocator>, dim3(n, shadow_split(p) / 4), dim3(256), 0, stream, p);
         });
     auto runs = [&](auto pooled, auto alone) {
         pieces([&](int n) {
