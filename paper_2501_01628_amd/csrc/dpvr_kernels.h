@@ -225,6 +225,7 @@ struct RqcParams {
     int32_t n;                  // bricks (ranks)
     int32_t tiles;              // 8 x 8 pixel tiles of all bricks' ROIs
     int32_t tile0;              // first tile of a launch of the shadow rays
+    int32_t split;              // wavefronts per tile of the shadow rays
     int32_t width, height;
     const RqcBrick* bricks;     // device, n
     long long n_entries;        // sum of ROI pixels over the bricks

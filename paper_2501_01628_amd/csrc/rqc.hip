@@ -27,6 +27,9 @@
 // composite's arithmetic, so the image equals the sort-last image exactly.
 #include "march_common.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace dpvr {
 namespace {
 
@@ -244,17 +247,18 @@ struct LightBrick {
 // The shadow rays of one 8 x 8 tile of a home brick's ROI: the ray of every
 // owned primary sample (its slot) cycles through the bricks home, home + 1,
 // ... (mod n), multiplying its transmittance by each one's.  A lane takes
-// every kShadowSplit-th sample of its pixel, so that a wavefront's 64 rays
-// start at one depth behind 8 x 8 neighbouring pixels: neighbouring lanes read
-// neighbouring voxels of a few rows.  (With the lanes on 64 consecutive
-// samples of one primary ray every lane read rows of its own, 33 cycles of
-// the L1 a load instead of 17.)  Bound by those vector loads, 4 a sample.
+// every split-th sample of its pixel (split: the wavefronts of a tile), so
+// that a wavefront's 64 rays start at one depth behind 8 x 8 neighbouring
+// pixels: neighbouring lanes read neighbouring voxels of a few rows.  (With the
+// lanes on 64 consecutive samples of one primary ray every lane read rows of
+// its own, 33 cycles of the L1 a load instead of 17.)  Bound by those vector
+// loads, 4 a sample.
 // Measured (96^3 in 6 bricks, 384x384, 896 M shadow and primary samples): the
 // frame 7.48 ms with one launch per cycle step and slot-ordered lanes, 3.49
 // so; 3.78 with the lanes in rows of 8.
-constexpr int kShadowSplit = 64;
+constexpr int kMaxShadowSplit = 64;
 
-__global__ __launch_bounds__(256) void rqc_shadow(RqcParams p) {
+__global__ __launch_bounds__(256, 5) void rqc_shadow(RqcParams p) {
     __shared__ TFTable tft;
     __shared__ LightBrick light[kMaxPartials];
     load_tf(tft, p.tf, p.dt, threadIdx.x, blockDim.x);
@@ -303,7 +307,7 @@ __global__ __launch_bounds__(256) void rqc_shadow(RqcParams p) {
         cr = camera_ray(p.cam, home.roi_x0 + lx, home.roi_y0 + ly);
     }
     unsigned long long evaluated = 0;
-    for (long long i = 4 * blockIdx.y + (threadIdx.x >> 6); i < slots; i += kShadowSplit) {
+    for (long long i = 4 * blockIdx.y + (threadIdx.x >> 6); i < slots; i += p.split) {
         RaySetup rs;
         {
 #pragma clang fp contract(off)
@@ -428,6 +432,18 @@ __global__ __launch_bounds__(256) void rqc_resolve(RqcParams p) {
         make_float4(fmaf(w, p.bg[0], C0), fmaf(w, p.bg[1], C1), fmaf(w, p.bg[2], C2), fmaf(w, p.bg[3], A));
 }
 
+// Wavefronts per tile of the shadow rays: 1.5 for each sample of the ROIs'
+// mean pixel (6 where tiles are few and their samples must fill the GPU), at
+// most kMaxShadowSplit; a lane past its pixel's samples only loads the tables.
+// Always 64, a frame of short rays spent its time on workgroups without work:
+// 32^3 in one brick at 1920x1080, step 8, 565 us, 149 so (256 at 6 a sample); in 4
+// bricks 1110 and 375; 96^3 in 6 bricks at 384x384, step 0.5, 3.50 ms either way;
+// 32^3 in 4 bricks at 96x72, step 0.5, 147 at 1.5, 111 at 6.
+int shadow_split(long long total, int tiles) {
+    const double mean = (double)total / (64.0 * tiles), each = tiles < 1024 ? 6.0 : 1.5;
+    return 4 * (int)std::min(kMaxShadowSplit / 4.0, 1.0 + std::ceil(each * mean / 4.0));
+}
+
 inline int grid_for(long long n, int per) { return (int)((n + per - 1) / per); }
 
 }  // namespace
@@ -455,10 +471,12 @@ long long rqc_scan_blocks(long long n_entries) { return scan_blocks(n_entries); 
 hipError_t launch_rqc_frame(RqcParams p, int cus, hipStream_t stream) {
     (void)cus;
     const long long npx = (long long)p.width * p.height;
-    if (p.shadows && p.total > 0)
+    if (p.shadows && p.total > 0) {
+        p.split = shadow_split(p.total, p.tiles);
         for (p.tile0 = 0; p.tile0 < p.tiles; p.tile0 += kMaxLaunchTiles)
-            hipLaunchKernelGGL(rqc_shadow, dim3(min(p.tiles - p.tile0, kMaxLaunchTiles), kShadowSplit / 4), dim3(256),
-                               0, stream, p);
+            hipLaunchKernelGGL(rqc_shadow, dim3(min(p.tiles - p.tile0, kMaxLaunchTiles), p.split / 4), dim3(256), 0,
+                               stream, p);
+    }
     const int tiles = (p.width + 7) / 8 * ((p.height + 7) / 8);
     hipLaunchKernelGGL(rqc_primary, dim3((tiles + 3) / 4, p.n), dim3(256), 0, stream, p);
     hipLaunchKernelGGL(rqc_resolve, dim3(grid_for(npx, 256)), dim3(256), 0, stream, p);
