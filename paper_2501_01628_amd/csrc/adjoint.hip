@@ -228,11 +228,12 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
             tacc[i] = 0.f;
         }
     };
-    // a' summed over samples, as sn + sf (a' above 1024, which leaves no
-    // transmittance, counts as 1024: sn stays small).  The integer part is
-    // split off before the addition: adding a whole dense a' to the fraction
-    // would round it at the size of that a', and the walk back would leave the
-    // rounding in front of the dense sample, where T_k is still near 1.
+    // a' summed over samples, as sn + sf (an a' above 160, which leaves no
+    // transmittance that float32 holds, counts as 160: sn fits an int for 13 M
+    // samples of a ray).  The integer part is split off before the addition:
+    // adding a whole dense a' to the fraction would round it at the size of
+    // that a', and the walk back would leave the rounding in front of the dense
+    // sample, where T_k is still near 1.
     int sn = 0;
     float sf = 0.0f;
     auto sum_a = [&](float a) {
@@ -242,7 +243,7 @@ __device__ __forceinline__ void backward_ray(const MarchParams& p, const Backwar
         sf -= carry;
         sn += (int)(most + carry);
     };
-    constexpr float kMostA = 1024.0f;
+    constexpr float kMostA = 160.0f;
     // forward: colour and transmittance of the stretch, and its sum of a'
     float C0 = 0.f, C1 = 0.f, C2 = 0.f, F = 1.f;
     auto ahead = [&](const auto& a) {

@@ -1234,9 +1234,6 @@ static vr_status prepare_backward(vr_context ctx, vr_brick b, const vr_partial* 
     bp.grad_tf = grad_tf;
     bp.grad_vox = grad_volume;
     p.ert_eps = 0.0f;
-    p.ckpt = const_cast<float*>(ckpt);
-    p.ckpt_interval = interval;
-    p.ckpt_nseg = (int32_t)ckpt_segments(b, ctx->dt, interval);
     p.samples = nullptr;
     return VR_OK;
 }
