@@ -1854,7 +1854,6 @@ TetPartK tetpart_tables(vr_tetpart q) {
     k.planes = reinterpret_cast<const double*>(q->ws + q->off[0]);
     k.planes32 = reinterpret_cast<const float*>(q->ws + q->off[11]);
     k.affine = reinterpret_cast<const double*>(q->ws + q->off[12]);
-    k.err32 = t.err32;
     k.vals = reinterpret_cast<const float*>(q->ws + q->off[1]);
     k.owned = reinterpret_cast<const uint32_t*>(q->ws + q->off[2]);
     k.cell_start = reinterpret_cast<const int32_t*>(q->ws + q->off[4]);
@@ -1864,6 +1863,7 @@ TetPartK tetpart_tables(vr_tetpart q) {
     k.bvh_nodes = reinterpret_cast<const int32_t*>(q->ws + q->off[8]);
     k.bvh_tets = reinterpret_cast<const int32_t*>(q->ws + q->off[9]);
     for (int c = 0; c < 3; ++c) {
+        k.err32[c] = t.err32[c];
         k.lo[c] = t.lo[c];
         k.hi[c] = t.hi[c];
         k.glo[c] = t.glo[c];

@@ -191,27 +191,29 @@ static void build_cell_heads(TetTables& out) {
     out.cell_head[4 * cells] = -1;
 }
 
-// The float32 barycentric planes.  With |x| <= X per axis (X: twice the
-// grid's largest extent, which holds the samples two steps beyond the box),
-// u = 2^-24, M = the sum of the three |m|_1 and |c_i| <= |m_i|_1 X (the plane
-// meets the box): rounding m, c and x costs 3 u |m_i|_1 X and the fused steps
-// 6 u |m_i|_1 X per coordinate, so 9 u M X for their sum and 6 u M X + 3 u for
-// the subtractions from one (M X >= 1); the float64 evaluation on both sides
-// 2^-49 M (X + |glo|).  16 u M X with the doubled extent bounds it twice over.
+// The float32 barycentric planes.  With |x_c| <= X_c on axis c (X_c: twice the
+// grid's extent there), u = 2^-24, |m_i|X = the sum of |m_ic| X_c, M = the sum
+// of the three |m_i|X, and |c_i| <= |m_i|X (the plane meets the box): rounding
+// m, c and x costs 3 u |m_i|X and the fused steps 6 u |m_i|X per coordinate, so
+// 9 u M for their sum and 6 u M + 3 u for the subtractions from one (M >= 1);
+// the float64 evaluation on both sides 2^-49 (M + the sum of |m_ic| |glo_c|).
+// 16 u M with the doubled extents bounds it twice over.  (Extents per axis, so
+// that a flat part's large coefficients across it meet its small extent there:
+// with the largest extent for all three nothing was decided in 61 K tetrahedra
+// of 1 x 1e-6 x 1, and 256x144 pixels took 236 us instead of 83 by float64
+// alone.)
 // A step longer than the part takes samples further out than X; there the
 // bound need not hold, but the test still cannot accept: it accepts coordinates
-// above the bound only, which sum to one, so the bound (32 u M times the extent
-// L) is below 1/4 and u M L below 1/128, each coordinate lies in (0, 1), and a
-// point at distance R per axis, being the true coordinates' combination of the
-// vertices, has R <= L + 15 u M R L, so R <= 1.14 L.  (Rejecting such a point
-// is right.)
+// above the bound only, which sum to one, so the bound, 16 u M, is below 1/4, u
+// times the sum of |m_ic| L_c (L_c = X_c / 2) below 1/128, and each coordinate
+// lies in (0, 1); with r the largest |x_c| / L_c the true coordinates differ from
+// them by less than 15/128 r in all, and the point, being their combination of
+// the vertices, has r <= 1 + 15/128 r, so r <= 1.14.  (Rejecting such a point is
+// right.)
 static void build_planes32(TetTables& out) {
-    double X = 0.0, G = 0.0;
-    for (int c = 0; c < 3; ++c) {
-        X = std::fmax(X, 2.0 * (double)out.gdim[c] / out.ginv[c]);
-        G = std::fmax(G, std::fabs(out.glo[c]));
-    }
-    out.err32 = (float)(16.0 * 0x1p-24 * X + 0x1p-48 * G) * 1.0001f;
+    for (int c = 0; c < 3; ++c)
+        out.err32[c] = (float)(16.0 * 0x1p-24 * 2.0 * (double)out.gdim[c] / out.ginv[c] +
+                               0x1p-48 * std::fabs(out.glo[c])) * 1.0001f;
     out.planes32.resize(12 * (size_t)out.n_tets);
     for (size_t e = 0; e < (size_t)out.n_tets; ++e) {
         double c[4], S = 0.0;

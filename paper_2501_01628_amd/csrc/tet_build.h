@@ -31,10 +31,11 @@ struct TetTables {
     // float32 for points x relative to glo: planes32[12 e + 4 i + (0, 1, 2, 3)]
     // = (mx, my, mz, c), coordinate i = m.x - c; coordinate 3 is one less their
     // sum.  For points of the box and its margin every one of the four is
-    // within err32 (sum over i of |mx| + |my| + |mz|) of D_i over the sum; a
-    // record whose values do not fit float32 has an infinite mx.
+    // within the sum over i of |mx| err32[0] + |my| err32[1] + |mz| err32[2] of
+    // D_i over the sum; a record whose values do not fit float32 has an infinite
+    // mx.
     std::vector<float> planes32;
-    float err32 = 0.0f;
+    float err32[3] = {0.0f, 0.0f, 0.0f};
     // bit i: a point with D_i = 0 counts as inside across face i (the tie
     // direction enters the tetrahedron there)
     std::vector<uint32_t> owned;

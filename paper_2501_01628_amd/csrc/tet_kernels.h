@@ -30,7 +30,7 @@ struct TetPartK {
     double glo[3], ginv[3];     // grid origin, cells per world unit
     int32_t gdim[3];
     int32_t n_tets;
-    float err32;                // error bound of the float32 planes (tet_build.h)
+    float err32[3];             // error bound of the float32 planes (tet_build.h)
     int32_t roi_x0, roi_y0, roi_w, roi_h;
     long long entry0;           // first frame entry of the part (its ROI pixels, row-major, after the previous parts')
     int32_t* rcount;            // roi_h x roi_w: runs of the pixel's ray

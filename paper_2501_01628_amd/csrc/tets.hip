@@ -136,9 +136,8 @@ __device__ inline int reject_face32(const TetPartK& P, const float4_t (&pl)[3], 
         const float4_t n = pl[i];
         l[i] = fmaf(n.x, x0, fmaf(n.y, x1, fmaf(n.z, x2, -n.w)));
         l[3] -= l[i];
-        e += fabsf(n.x) + fabsf(n.y) + fabsf(n.z);
+        e = fmaf(fabsf(n.x), P.err32[0], fmaf(fabsf(n.y), P.err32[1], fmaf(fabsf(n.z), P.err32[2], e)));
     }
-    e *= P.err32;
     const float least = fminf(fminf(l[0], l[1]), fminf(l[2], l[3]));
     const int face = l[0] == least ? 0 : l[1] == least ? 1 : l[2] == least ? 2 : 3;
     return least + e < 0.0f ? face : least - e > 0.0f ? -1 : kUndecided;

@@ -55,9 +55,8 @@ static int pretest(const TetTables& t, int e, const double p[3]) {
         const float* n = &t.planes32[12 * (size_t)e + 4 * i];
         l[i] = fmaf(n[0], x[0], fmaf(n[1], x[1], fmaf(n[2], x[2], -n[3])));
         l[3] -= l[i];
-        sum += std::fabs(n[0]) + std::fabs(n[1]) + std::fabs(n[2]);
+        sum = fmaf(std::fabs(n[0]), t.err32[0], fmaf(std::fabs(n[1]), t.err32[1], fmaf(std::fabs(n[2]), t.err32[2], sum)));
     }
-    sum *= t.err32;
     const float least = std::fmin(std::fmin(l[0], l[1]), std::fmin(l[2], l[3]));
     return least + sum < 0.0f ? 1 : least - sum > 0.0f ? -1 : 0;
 }
