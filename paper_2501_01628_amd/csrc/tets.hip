@@ -279,6 +279,7 @@ __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, do
     };
     place();
     while (left >= 0) {
+        const bool walking = kLocator == kTetBvh && __any(cand >= 0);
         int settle = 0;                                  // samples to go on by
         int found = -1;
         // (a point outside the grid takes the head after the last cell's, of
@@ -317,10 +318,14 @@ __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, do
                 if (cand < 0) settle = 1;                // the cell's list is through
             }
         } else if (kLocator == kTetBvh) {
-            double p[3];
-            point(p);
-            found = bvh_locate(P, p[0], p[1], p[2]);
-            settle = 1;
+            // (once every lane waits for it: the hierarchy is searched by all of
+            // them at once)
+            if (!walking) {
+                double p[3];
+                point(p);
+                found = bvh_locate(P, p[0], p[1], p[2]);
+                settle = 1;
+            }
         } else if (aux.x < 0) {
             settle = 1 + (int)((float)(-aux.x - 1) * per_cell);
         } else {
