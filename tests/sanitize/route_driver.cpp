@@ -268,7 +268,7 @@ int main() {
     {
         int tiles = 0;
         EXPECT(tet_route(1, 640, 640, 0.25, &tiles) == 0 && tiles == 6400);
-        EXPECT(tet_route(1, 800, 800, 0.25, &tiles) == 1 && tiles == 10000);
+        EXPECT(tet_route(1, 800, 800, 0.2, &tiles) == 1 && tiles == 10000);
         EXPECT(tet_route(1, 800, 800, 0.125, &tiles) == 0 && tiles == 10000);
         EXPECT(tet_route(2, 904, 904, 0.01, &tiles) == 0 && tiles == 25538);
         EXPECT(tet_route(3, 800, 800, 0.01, &tiles) == 1 && tiles == 30000);

@@ -16,7 +16,7 @@ LIGHT, AMBIENT = (1.0, 0.4, -0.2), 0.3
 
 @pytest.mark.parametrize("locator", [0, 1], ids=["grid", "bvh"])
 @pytest.mark.parametrize("name,cells,nparts,dt,size", [
-    ("few samples across", (4, 4, 4), 1, 0.9, (1003, 807)),      # 12,726 tiles, 4.4 samples
+    ("few samples across", (4, 4, 4), 1, 0.9, (1003, 807)),      # 12,726 tiles, a mean chord of 3 samples
     ("many tiles", (5, 4, 3), 4, 0.27, (1211, 973)),             # four parts over most of 152 x 122 tiles
 ])
 def test_sampled_pixels(name, cells, nparts, dt, size, locator):
