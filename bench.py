@@ -44,7 +44,8 @@ def parse():
     ap.add_argument("--storage", choices=["f32", "f16"], default=None,
                     help="brick storage (default f32; c5 is a float16 workload: f16)")
     ap.add_argument("--path", choices=["staged", "direct"], default="staged",
-                    help="march from LDS-staged slices or straight from HBM (same images)")
+                    help="the library's choice (LDS-staged slices, or straight from HBM where that is "
+                         "faster), or straight from HBM (same images)")
     ap.add_argument("--staging", choices=["slab", "ring"], default=None,
                     help="staged march family: all waves stage a slab then march it, or a producer "
                          "wave streams slices into an LDS ring ahead of the marching waves "
@@ -677,7 +678,7 @@ def bench_adjoint(args):
     r.close()
     del r
     torch.cuda.empty_cache()
-    evals = 3     # checkpointed forward, segment re-march, adjoint walk
+    evals = 3     # checkpointed forward, the backward's walk forward, its walk back
     lane_ops = samples * evals * VALU_LANE_OPS_PER_SAMPLE
     achieved = lane_ops / (step_ms * 1e-3)
     peak = VALU_LANES_PER_CU_CYCLE * N_CU * CLOCK_HZ
@@ -693,7 +694,7 @@ def bench_adjoint(args):
                         "frac": achieved / peak, "traffic": None,
                         "model": f"{VALU_LANE_OPS_PER_SAMPLE} VALU lane-ops per sample evaluation, "
                                  f"{evals} evaluations per owned sample per step (checkpointed forward, "
-                                 f"segment re-march, adjoint walk); peak = 64 lanes/CU/cycle x 256 CUs "
+                                 f"the backward's walk forward and back); peak = 64 lanes/CU/cycle x 256 CUs "
                                  f"x 2.4 GHz, unpacked fp32"}}
     out["cpu_baseline"] = None
     if not args.no_cpu_baseline:
@@ -820,7 +821,7 @@ def bench_rqc(args):
                                   f"{W}x{H} perspective, step 0.5, opacity 0.25, light {light}, ambient {ambient}"},
            "samples_per_frame": samples, "primary_samples_per_frame": total,
            "ms_without_shadows": ms_plain, "ms_sort_last": ms_sortlast,
-           "roofline": {"kernel": "rqc_shadow_step x 6 + rqc_primary_step x 6 + rqc_resolve", "bound": "alu",
+           "roofline": {"kernel": "rqc_shadow + rqc_primary + rqc_resolve", "bound": "alu",
                         "achieved": achieved, "peak": peak, "unit": "lane-op/s", "frac": achieved / peak,
                         "traffic": None,
                         "model": f"{VALU_LANE_OPS_PER_SAMPLE} VALU lane-ops per evaluated sample; peak = 64 "
@@ -971,12 +972,13 @@ def tet_scene(cells=(128, 96, 96), n_parts=16, width=1920, height=1080):
     return vals, parts, cam, len(t), len(v)
 
 
-# fp64 operations per held sample in the tetrahedral march when the first
-# tetrahedron tested holds it: the sample position (t = (k + 1/2) dt, p = o +
-# t d: 8), four face sub-volumes (3 multiplies + 3 adds each: 24) and the
-# barycentric value (3 adds for the sum, 4 multiplies + 3 adds, 1 divide: 11)
-TET_FP64_OPS_PER_SAMPLE = 43
-FP64_VECTOR_PEAK = 78.6e12
+# operations per held sample in the tetrahedral march when the first
+# tetrahedron tested holds it: fp64, the sample position (t = (k + 1/2) dt, p =
+# o + t d, x = p - origin: 11) and the affine value (6); fp32, three barycentric
+# coordinates (3 fma each), the fourth (3) and the error bound (9 fma): 39.  Both
+# at the vector rate that fp64 and unpacked fp32 share.
+TET_OPS_PER_SAMPLE = 56
+VECTOR_PEAK = 78.6e12
 
 
 def mixed_scene(cells=(96, 72, 72), n_parts=16, width=1920, height=1080):
@@ -1054,7 +1056,7 @@ def bench_tets(args):
     log(f"timed {args.steps} frames: {ms_per_step:.3f} ms/frame, march {march_ms:.3f} ms, resolve "
         f"{resolve_ms:.3f} ms, {held} held samples/frame")
     W, H = cam["width"], cam["height"]
-    achieved = held * TET_FP64_OPS_PER_SAMPLE / (march_ms * 1e-3)
+    achieved = held * TET_OPS_PER_SAMPLE / (march_ms * 1e-3)
     if mixed:
         wl = (f"tets-mixed: {n_cells} cells (hexahedra, wedges, pyramids, tetrahedra of jittered 96x72x72 "
               f"cubes; {n_tets} tetrahedra after the cut, {n_verts} vertices), 8 blobs, {len(parts)} non-convex "
@@ -1072,11 +1074,11 @@ def bench_tets(args):
            "host_table_build_s": host_build_s, "device_table_bytes": table_bytes,
            "grid_entries_per_tet": grid_entries / n_tets,
            "roofline": {"kernel": "tet_march", "bound": "alu", "achieved": achieved / 1e12,
-                        "peak": FP64_VECTOR_PEAK / 1e12, "unit": "TFLOP/s", "frac": achieved / FP64_VECTOR_PEAK,
+                        "peak": VECTOR_PEAK / 1e12, "unit": "TFLOP/s", "frac": achieved / VECTOR_PEAK,
                         "traffic": None,
-                        "model": f"{TET_FP64_OPS_PER_SAMPLE} fp64 operations per held sample (position, four "
-                                 f"face sub-volumes, barycentric value) over the march launch; peak = fp64 "
-                                 f"vector 78.6 TFLOP/s"}}
+                        "model": f"{TET_OPS_PER_SAMPLE} operations per held sample (17 fp64: position, affine "
+                                 f"value; 39 fp32: the test) over the march launch; peak = vector 78.6 TFLOP/s "
+                                 f"(fp64 and unpacked fp32)"}}
     out["cpu_baseline"] = None
     if not args.no_cpu_baseline:
         import oracle
@@ -1129,7 +1131,7 @@ def bench_tets_shadow(args):
     """Shadow rays through tetrahedral parts: a 64x48x48-cube box (884,736
     tetrahedra, jitter 0.15), 8 blobs, 8 smooth non-convex parts, 768x768
     orbit view, step 0.5, opacity 0.1, light (0.8, 1.0, -0.4), ambient 0.3.
-    One step = record + 8 shadow cycle steps + shaded march + resolve (the
+    One step = record + shadow rays + shaded march + resolve (the
     plan, which depends on geometry and camera only, is made once)."""
     import torch
 
@@ -1172,7 +1174,7 @@ def bench_tets_shadow(args):
     ms_plain = e0.elapsed_time(e1) / args.steps
     r.close()
     log(f"shadowed frame {ms:.3f} ms ({total} primary + {samples - total} shadow samples), unshadowed {ms_plain:.3f} ms")
-    achieved = samples * TET_FP64_OPS_PER_SAMPLE / (ms * 1e-3)
+    achieved = samples * TET_OPS_PER_SAMPLE / (ms * 1e-3)
     W, H = cam["width"], cam["height"]
     out = {"metric": "Msamples/s (tetrahedral parts with shadow rays: primary + shadow samples held per frame x "
                      "frames/s)",
@@ -1183,10 +1185,10 @@ def bench_tets_shadow(args):
                                   f"non-convex parts, {W}x{H} perspective, step 0.5, opacity 0.1, light {light}, "
                                   f"ambient {a0}"},
            "samples_per_frame": samples, "primary_samples_per_frame": total, "ms_without_shadows": ms_plain,
-           "roofline": {"kernel": "tet_march<record> + tet_shadow_step x 8 + tet_march<shaded> + tet_resolve",
-                        "bound": "alu", "achieved": achieved / 1e12, "peak": FP64_VECTOR_PEAK / 1e12,
-                        "unit": "TFLOP/s", "frac": achieved / FP64_VECTOR_PEAK, "traffic": None,
-                        "model": f"{TET_FP64_OPS_PER_SAMPLE} fp64 operations per held (primary or shadow) sample "
+           "roofline": {"kernel": "tet_march<record> + tet_shadow + tet_march<shaded> + tet_resolve",
+                        "bound": "alu", "achieved": achieved / 1e12, "peak": VECTOR_PEAK / 1e12,
+                        "unit": "TFLOP/s", "frac": achieved / VECTOR_PEAK, "traffic": None,
+                        "model": f"{TET_OPS_PER_SAMPLE} operations per held (primary or shadow) sample "
                                  f"over the frame; peak = fp64 vector 78.6 TFLOP/s"}}
     out["cpu_baseline"] = None
     if not args.no_cpu_baseline:

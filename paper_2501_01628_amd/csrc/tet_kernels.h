@@ -20,7 +20,7 @@ struct TetPartK {
     const double* affine;       // 2 x n_tets x 2: (gx, gy), then (gz, c): value g . x + c of a point x relative to glo
     const float* vals;          // n_tets x 4: vertex values in vertex order (16-byte aligned)
     const uint32_t* owned;      // n_tets: tie-rule bits
-    const int32_t* cell_start;  // grid cells + 1
+    const int32_t* cell_start;  // grid cells + 1 (for checks of the layout; the kernels read the heads)
     const int32_t* cell_tets;
     const int32_t* cell_head;   // (grid cells + 1) x 4: each cell's head (tet_build.h)
     const int32_t* nbr;         // n_tets x 4: tetrahedron across each face (-1: none in the part)
