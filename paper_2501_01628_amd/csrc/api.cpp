@@ -740,7 +740,12 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
 //   than one per CU from many bricks of 1 MB and more at more than 5.4 voxels a
 //   pixel (294 to 500 tiles at 6.2 to 7.5 at the centre: 64 to 216 bricks of 1.2 MB 0.70 to
 //   0.92, of 4 and 8 MB 0.70 to 0.97, of 32 MB 0.86; of 0.5 to 0.95 MB 1.5 to 2.0; at
-//   5.5 1.23; 27 bricks of 32 MB on 158 tiles at 10.4 1.6);
+//   5.5 1.23; 27 bricks of 32 MB on 158 tiles at 10.4 1.6; volumes of 256^3 to
+//   640^3 in 1 to 16 bricks at 49 to 535 tiles, steps 0.5 and 1: float32 1.02 to
+//   2.4, float16 0.87 to 3.6, below 0.97 in 12 of 352 views, all of bricks of 33 MB
+//   and more at 3 voxels a pixel and more, where the mean is still 1.02 to 1.2;
+//   bricks with slices beyond 8 MiB, marched by 64-bit addresses, 3000 x 1500 x
+//   60 at 200x150 to 480x360, 1.7 to 2.0, float16 1.0 to 3.3);
 // * for float32 bricks seen at few voxels a pixel, where the lanes of a
 //   wavefront share the lines they read: up to sqrt(1.28 step) voxels a pixel
 //   with the step in voxels, since a coarse step has fewer samples per staged

@@ -5,7 +5,7 @@
 // A frame, for n parts and the context camera:
 //   march     one workgroup per 8 x 8 tile of a part's ROI (the part's
 //             bounding box projected), its wavefronts taking stretches of the
-//             tile's rays.
+//             tile's rays, or, where tiles are many, one wavefront per tile.
 //             Every lattice sample t_k = (k + 1/2) dt of the ray inside the
 //             part's bounding box is located in the part: by a short walk
 //             from the tetrahedron that held the ray's previous sample (to the
@@ -204,7 +204,10 @@ __device__ inline float tet_value(const TetPartK& P, int e, const double x[3], c
 // The records of a part's affine values: value(x) = g . x + c with x
 // relative to the grid origin, from the planes and the vertex values
 // (v0 + sum (v_i - v0) D_i(x) / sum D_i; the D_i sum to the same volume at
-// every x).
+// every x).  Bound by memory: 176 bytes a tetrahedron.  Once per time step of a
+// part: 2.0 M tetrahedra in one part, setting the values 17 us without the
+// records, 77 with them (8 parts 47 and 117), for a 1280x720 frame of 2.35 ms
+// before and 0.72 now (3.9 and 1.7), 96x72 pixels of 246 K 1.30 and 0.27.
 __global__ __launch_bounds__(256) void tet_affine(TetPartK P, double2_t* __restrict__ out) {
 #pragma clang fp contract(off)
     const int e = blockIdx.x * 256 + threadIdx.x;
@@ -601,13 +604,14 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
     count_held(f.samples, counted);
 }
 
-// The shadow rays of one tile of a home part's ROI (the tiles of the march): the ray of every held primary sample (its slot) cycles through
-// the parts home, home + 1, ... (mod n), multiplying its transmittance by
-// each one's.  A lane takes every split-th held sample of its pixel (split: the
-// wavefronts of a tile, from its wavefront's place among them), so that a wavefront's 64 rays start at the same depth
-// behind 8 x 8 neighbouring pixels and cross the same tetrahedra; with the
-// lanes on 64 consecutive samples of one primary ray their loads touched as
-// many lines as lanes.
+// The shadow rays of one tile of a home part's ROI (the tiles of the march):
+// the ray of every held primary sample (its slot) cycles through the parts
+// home, home + 1, ... (mod n), multiplying its transmittance by each one's.  A
+// lane takes every split-th held sample of its pixel (split: the wavefronts of
+// a tile, from its wavefront's place among them), so that a wavefront's 64 rays
+// start at the same depth behind 8 x 8 neighbouring pixels and cross the same
+// tetrahedra; with the lanes on 64 consecutive samples of one primary ray their
+// loads touched as many lines as lanes.
 constexpr int kMaxShadowSplit = 256;
 
 template <int kLocator>
