@@ -2151,26 +2151,32 @@ struct TetShadowArgs {
 
 // Whether a frame's tiles take a wavefront each rather than a workgroup whose
 // wavefronts share their rays: a workgroup a tile costs 3 ns of the GPU however
-// little its rays hold, a wavefront alone waits for the slowest of its rays.
-// A wavefront is the better one for many tiles: from 28000 on, and from 10000
-// (6000) on with at most 3.4 (1.5) samples on a box's mean chord (4 volumes over
-// the surface, 2/3 of a cube's edge).  Workgroup over wavefront time, meshes of 16^3 to 64^3 cells,
-// chords of 85 samples or more down to one: 6400 tiles 0.63 to 1.3, at 1.5 and
-// fewer 0.87 to 1.1, 14000 0.67 to 1.4, there at 3.4 and fewer 0.95 to 1.3; 25000 0.75 to 1.2, at 3.4 and fewer 1.1
-// to 1.6; 30000 1.03 to 1.5; 56000 0.98 to 2.3; plates of 40 x 40 x 0.02 to 0.2 at
-// 1280x720, step 0.5, 1.5.  24^3 cells in 10 parts at 1280x720, step 8: 269 and 183 us,
-// 172 when a workgroup took four tiles in step.
+// little its rays hold, a wavefront alone waits for the slowest of its rays and
+// meets its tetrahedra in a cache that more tiles share.  A wavefront is the
+// better one for many tiles, the more of them the larger the mesh: from 28000
+// and 400 times the cube root of its tetrahedra on, and from 10000 (6000) on with
+// at most 3.4 (1.5) samples on a box's mean chord (4 volumes over the surface,
+// 2/3 of a cube's edge).  Workgroup over wavefront time, meshes of 16^3 to 80 x
+// 64 x 64 cells in 1 to 16 parts, steps 0.25 to 6: 6400 tiles 0.63 to 1.3, at 1.5
+// samples and fewer 0.87 to 1.1; 14000 0.67 to 1.4, at 3.4 and fewer 0.95 to 1.3;
+// 25000 0.75 to 1.2, at 3.4 and fewer 1.1 to 1.6; 30000 and more, above the line
+// 0.89 to 2.3 (below 0.94 in one view of 60), below it 0.87 to 1.3.  7.1 M
+// tetrahedra in 5 and 16 parts (line at 77000): at 27000 to 50000 tiles 0.48 to
+// 1.1, at 72000 0.83 to 1.2, at 127000 1.0 to 1.3.  Plates of 40 x 40 x 0.02 to
+// 0.2 at 1280x720, step 0.5, 1.5.  24^3 cells in 10 parts at 1280x720, step 8: 269
+// and 183 us, 172 when a workgroup took four tiles in step.
 static bool tet_alone(int32_t n, const vr_tetpart* parts, const std::vector<int32_t>& prefix, double dt) {
-    double chords = 0.0;
+    double chords = 0.0, tets = 0.0;
     const double tiles = prefix[n];
     for (int i = 0; i < n; ++i) {
         if (prefix[i + 1] == prefix[i]) continue;
         const TetTables& t = parts[i]->tab;
+        tets += t.n_tets;
         const double a = t.hi[0] - t.lo[0], b = t.hi[1] - t.lo[1], c = t.hi[2] - t.lo[2];
         const double surface = 2.0 * (a * b + b * c + c * a);
         if (surface > 0.0) chords += (prefix[i + 1] - prefix[i]) * (4.0 * a * b * c / surface / dt);
     }
-    return tiles >= 28000.0 || (tiles >= 10000.0 && chords <= 3.4 * tiles) || (tiles >= 6000.0 && chords <= 1.5 * tiles);
+    return (tiles >= 28000.0 && tiles >= 400.0 * std::cbrt(tets)) || (tiles >= 10000.0 && chords <= 3.4 * tiles) || (tiles >= 6000.0 && chords <= 1.5 * tiles);
 }
 
 // The frame of n parts, `stages` a mask of the kTet* stages (march into the

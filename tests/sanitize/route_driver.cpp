@@ -151,12 +151,24 @@ struct Setup {
     }
 };
 
-// A cube of one tetrahedron-filled cell per part, `copies` of it over each
-// other (each its own part), filling an image of the given size; 1 if a
-// wavefront takes a tile.
-static int tet_route(int copies, int width, int height, double dt, int* tiles) {
-    const double v[24] = {0, 0, 0, 0, 0, 1, 0, 1, 0, 0, 1, 1, 1, 0, 0, 1, 0, 1, 1, 1, 0, 1, 1, 1};
-    const int32_t t[24] = {0, 4, 6, 7, 0, 4, 5, 7, 0, 2, 6, 7, 0, 2, 3, 7, 0, 1, 5, 7, 0, 1, 3, 7};
+// A unit cube of cells^3 cells cut into tetrahedra per part, `copies` of it
+// over each other (each its own part), filling an image of the given size; 1 if
+// a wavefront takes a tile.
+static int tet_route(int copies, int width, int height, double dt, int* tiles, int cells = 1) {
+    const int n = cells + 1, step[3] = {n * n, n, 1};
+    const int order[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+    std::vector<double> v;
+    std::vector<int32_t> t;
+    for (int i = 0; i < n * n * n; ++i)
+        for (int c = 0; c < 3; ++c) v.push_back((double)(i / step[c] % n) / cells);
+    for (int i = 0; i < n * n * n; ++i) {
+        if (i / step[0] == cells || i / step[1] % n == cells || i % n == cells) continue;
+        for (const auto& o : order) {
+            int32_t w = i;
+            t.push_back(w);
+            for (int c : o) t.push_back(w += step[c]);
+        }
+    }
     vr_context ctx = nullptr;
     EXPECT(vr_context_create(0, nullptr, &ctx) == VR_OK);
     void* img = buf((size_t)16 * width * height);
@@ -166,10 +178,10 @@ static int tet_route(int copies, int width, int height, double dt, int* tiles) {
     EXPECT(vr_set_camera_orthographic(ctx, pos, dir, up, 0.5, width, height) == VR_OK);
     std::vector<vr_tetpart> parts;
     std::vector<void*> mem;
-    const float vals[8] = {};
+    const std::vector<float> vals(v.size() / 3);
     for (int i = 0; i < copies; ++i) {
         vr_tetpart q = nullptr;
-        EXPECT(vr_tetpart_create(ctx, v, 8, t, 6, &q) == VR_OK);
+        EXPECT(vr_tetpart_create(ctx, v.data(), (int32_t)(v.size() / 3), t.data(), (int32_t)(t.size() / 4), &q) == VR_OK);
         double lo[3], hi[3];
         int32_t grid[3];
         int64_t count;
@@ -178,7 +190,7 @@ static int tet_route(int copies, int width, int height, double dt, int* tiles) {
         EXPECT(vr_tetpart_info(q, lo, hi, grid, &count, &bytes, &nt) == VR_OK);
         mem.push_back(buf(bytes));
         EXPECT(vr_tetpart_attach(q, mem.back(), bytes) == VR_OK);
-        EXPECT(vr_tetpart_set_values(q, vals) == VR_OK);
+        EXPECT(vr_tetpart_set_values(q, vals.data()) == VR_OK);
         parts.push_back(q);
     }
     size_t need = 0;
@@ -272,6 +284,9 @@ int main() {
         EXPECT(tet_route(1, 800, 800, 0.125, &tiles) == 0 && tiles == 10000);
         EXPECT(tet_route(2, 904, 904, 0.01, &tiles) == 0 && tiles == 25538);
         EXPECT(tet_route(3, 800, 800, 0.01, &tiles) == 1 && tiles == 30000);
+        // 827,052 tetrahedra in all: from 37,546 tiles on
+        EXPECT(tet_route(2, 1080, 1080, 0.01, &tiles, 41) == 0 && tiles == 36450);
+        EXPECT(tet_route(2, 1120, 1120, 0.01, &tiles, 41) == 1 && tiles == 39200);
     }
     std::printf("%s: %d failed expectations\n", g_fail ? "FAIL" : "OK", g_fail);
     return g_fail ? 1 : 0;
