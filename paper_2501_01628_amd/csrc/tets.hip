@@ -158,7 +158,10 @@ __device__ inline void count_held(unsigned long long* counter, unsigned long lon
 // The tetrahedron of part P that holds p (-1: none), by the BVH: from the
 // root, a node whose box holds p is entered (its first child follows it; a
 // leaf's tetrahedra are tested), any other is skipped through its skip link.
+// (A leaf's tetrahedra by the float32 planes first: with the float64 ones alone,
+// 128 bytes a test for 48, frames took 1.2 to 1.3 times as long.)
 __device__ inline int bvh_locate(const TetPartK& P, double p0, double p1, double p2) {
+    const float x0 = (float)(p0 - P.glo[0]), x1 = (float)(p1 - P.glo[1]), x2 = (float)(p2 - P.glo[2]);
     double D[4];
     int node = P.n_tets > 0 ? 0 : -1;
     while (node >= 0) {
@@ -173,7 +176,11 @@ __device__ inline int bvh_locate(const TetPartK& P, double p0, double p1, double
             const int first = leaf >> 3, count = leaf & 7;
             for (int i = 0; i < count; ++i) {
                 const int e = ((gint*)P.bvh_tets)[first + i];
-                if (reject_face(P, e, p0, p1, p2, D) < 0) return e;
+                gfloat4* rec = ((gfloat4*)P.planes32) + 3 * (long long)e;
+                const float4_t pl[3] = {rec[0], rec[1], rec[2]};
+                int face = reject_face32(P, pl, x0, x1, x2);
+                if (face == kUndecided) face = reject_face(P, e, p0, p1, p2, D);
+                if (face < 0) return e;
             }
             node = skip;
         } else {
@@ -256,7 +263,17 @@ __global__ __launch_bounds__(256) void tet_affine(TetPartK P, double2_t* __restr
 // of its 64 lanes at every sample).  A sample in an empty cell, d cells from
 // the nearest listed one, also settles the following ones that stay within
 // d - 1 cells of it.
-template <int kLocator, bool kValues, typename Held, typename Gap>
+//
+// The BVH's lanes wait for each other instead, since a search of the hierarchy
+// costs by the nodes that any lane of the wavefront meets: kInStep, every lane at
+// its next sample; else a lane waits until none of the wavefront walks, and all
+// waiting ones search at once.  In step takes 0.84 to 0.92 of the time of waiting
+// where tiles go to a wavefront each (24^3 to 128 x 96 x 96 cells in 3 to 16 parts,
+// 28000 tiles and more; one part of 80 x 64 x 64 1.27), 0.98 to 1.56 in stretches.
+// One lane a ray with float64 planes, then waiting with them in the leaves, and
+// as here: 7.1 M in 16 parts at 1920x1080 35.5, 39.4 and 28.6 ms, 2.0 M in 16 at
+// 2560x1440 27.1, 34.6 and 25.6, 83 K in 6 at 2560x1440 5.69, 6.96 and 5.33.
+template <int kLocator, bool kValues, bool kInStep, typename Held, typename Gap>
 __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, double dt, long long k0, long long k1,
                                           Held held, Gap gap) {
 #pragma clang fp contract(off)
@@ -280,6 +297,31 @@ __device__ __forceinline__ void walk_part(const TetPartK& P, const CamRay& r, do
         point(p);
         for (int c = 0; c < 3; ++c) x[c] = p[c] - P.glo[c];
     };
+    if constexpr (kLocator == kTetBvh && kInStep) {
+        for (; left >= 0; --left, k += 1.0) {
+            double p[3], D[4];
+            place();
+            point(p);
+            int found = -1;
+            for (walk = kWalkSteps; cand >= 0;) {
+                const int4_t aux = *(gint4_unaligned*)((gint*)P.nbr + 4 * (long long)cand);
+                gfloat4* rec = ((gfloat4*)P.planes32) + 3 * (long long)cand;
+                const float4_t pl[3] = {rec[0], rec[1], rec[2]};
+                int face = reject_face32(P, pl, (float)x[0], (float)x[1], (float)x[2]);
+                if (face == kUndecided) face = reject_face(P, cand, p[0], p[1], p[2], D);
+                if (face < 0) {
+                    found = cand;
+                    break;
+                }
+                cand = --walk > 0 ? (face == 0 ? aux.x : face == 1 ? aux.y : face == 2 ? aux.z : aux.w) : -1;
+            }
+            if (found < 0) found = bvh_locate(P, p[0], p[1], p[2]);
+            if (found >= 0) held(k, kValues ? tet_value(P, found, x, p) : 0.0f);
+            else gap();
+            cand = found;
+        }
+        return;
+    }
     place();
     while (left >= 0) {
         const bool walking = kLocator == kTetBvh && __any(cand >= 0);
@@ -452,7 +494,7 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
     }
     if constexpr (!kRuns) {
         unsigned long long held = 0;
-        walk_part<kLocator, false>(P, r, f.dt, k0, k1, [&](double k, float) {
+        walk_part<kLocator, false, true>(P, r, f.dt, k0, k1, [&](double k, float) {
             // the passes locate alike, so a ray holds as many samples as
             // counted; a mismatch (which only a logic error could cause) is
             // reported and never writes outside the ray's slots
@@ -521,7 +563,7 @@ __global__ __launch_bounds__(tet_runs<kMode>() ? 64 * kWaves : 64, 5) void tet_m
             ++nrun;
             in_run = false;
         };
-        walk_part<kLocator, true>(P, r, f.dt, ka, kb, [&](double sample, float v) {
+        walk_part<kLocator, true, kAlone>(P, r, f.dt, ka, kb, [&](double sample, float v) {
 #pragma clang fp contract(off)
             const int k = (int)sample;
             if (!in_run) {
@@ -655,7 +697,7 @@ __global__ __launch_bounds__(256, 5) void tet_shadow(TetFrameParams f) {
                 if (f.err) atomicOr(f.err, kErrRange);
                 j1 = j0 - 1;
             }
-            walk_part<kLocator, true>(at, sr, f.dt, j0, j1, [&](double, float v) {
+            walk_part<kLocator, true, false>(at, sr, f.dt, j0, j1, [&](double, float v) {
                 S = S * trans_exp2(-classify(tft, v, tf_k, tf_o).a);
                 ++evaluated;
             }, []() {});
