@@ -753,14 +753,17 @@ __global__ __launch_bounds__(256) void tet_resolve(TetFrameParams f) {
 }
 
 // Wavefronts per tile of the shadow rays: 6 for each held sample of the ROIs'
-// mean pixel, at most kMaxShadowSplit (a lane past its pixel's samples only
-// loads the table, but a pixel may hold many times the mean).  Always 256, a
-// frame of short rays spent its time on workgroups without work: 16^3 cells in 4
-// parts at 800x600, step 8, 1571 us, 289 so; step 0.5 4.51 and 3.46 ms; 40^3 in 4
-// parts at 384x288, step 0.5, 5.48 and 5.45 (2.5 a sample: 5.66).
+// mean pixel (24 where tiles are few, and the GPU waits for the fullest pixel), at
+// most kMaxShadowSplit (a lane past its pixel's samples only loads the table, but
+// a pixel may hold many times the mean).  Always 256, a frame of short rays spent
+// its time on workgroups without work: 16^3 cells in 4 parts at 800x600, step 8,
+// 1571 us, 289 so; step 0.5 4.51 and 3.46 ms; 40^3 in 4 parts at 384x288, step 0.5,
+// 5.48 and 5.45 (2.5 a sample: 5.66).  27 x 23 x 17 in 4 parts at 172x135, step
+// 0.5, 1.41 ms at 256, 1.60 at 6 a sample.
 int shadow_split(const TetFrameParams& p) {
     const double mean = (double)p.total / ((double)kTetTile * kTetTile * p.total_tiles);
-    return 4 * (int)std::min(kMaxShadowSplit / 4.0, 1.0 + std::ceil(6.0 * mean / 4.0));
+    const double each = p.total_tiles < 1024 ? 24.0 : 6.0;
+    return 4 * (int)std::min(kMaxShadowSplit / 4.0, 1.0 + std::ceil(each * mean / 4.0));
 }
 
 template <int kLocator>
