@@ -766,20 +766,22 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
 //   at 4 0.70 to 0.8; of 2.2 MB at 1.6 1.07 to 1.17, at 2.2 0.91 to 1.02, at 4
 //   0.81 to 0.86), and of twice that up to 1.6 of the line above (4.2 MB at 1.2,
 //   step 0.5, 1.25; 8 MB at 1.0, step 0.5, 1.1).  float16: up to 8 MB from
-//   1 / sqrt(step) voxels a pixel on, where few samples share a staged voxel (0.08
-//   to 8 MB, a hundred volumes from all sides: step 0.25 at 1.0 to 1.5 0.60 to 1.3,
-//   the median 0.93, at 2 to 3 0.84 to 1.5, 1.2; step 0.5 at 1.0 to 1.2 0.81 to
-//   1.4, 1.02, at 1.5 to 3 1.0 to 2.2, 1.35; step 1 at 1.0 to 1.2 1.03 to 2,
-//   1.3), at a step below half a voxel up to 3 MB and 30 MB of brick x (voxels a
-//   pixel)^2 (step 0.25: of 0.6 MB at 4 1.4, at 5.5 and 7.5 0.98; of 1.1 MB at 4
-//   1.3, at 7.5 0.73; of 2.1 MB at 3 1.12, at 4 0.90; of 4 MB at 1.2 to 1.6 0.85
+//   1 / sqrt(step) voxels a pixel on, where few samples share a staged voxel, and
+//   up to 1 MB from one on at half a voxel a step or more (a hundred volumes from
+//   all sides: step 0.5, 1 to 8 MB, at 1.0 to 1.2 0.80 to 1.3, the median 0.99, at
+//   1.5 to 3 1.0 to 2.2, 1.35; up to 1 MB at 1.0 to 1.2 0.88 to 1.5, 1.1, batches
+//   1.35 and 1.6; step 1 at 1.0 to 1.2 1.03 to 2, 1.3); at a step below half a
+//   voxel from 0.75 / sqrt(step) on (step 0.25 at 1.0 to 1.5 0.60 to 1.3, 0.93; at
+//   1.5 to 3 0.84 to 1.5, 1.1) up to 3 MB and 30 MB of brick x (voxels a pixel)^2
+//   (of 0.6 MB at 4 1.4, at 5.5 and 7.5 0.98; of 1.1 MB at 4 1.3, at 7.5 0.73; of
+//   2.1 MB at 3 1.12, at 4 0.90; of 4 MB at 1.2 to 1.6 0.85
 //   to 0.89).
 // Views along y whose pixel rows run along z, where neighbouring lanes share no
 // line, count twice the voxels a pixel in the lines of float32 (bricks to 30 MB
 // at 0.4 of the line 1.1 to 1.9, at 0.6 0.7 to 1.3, at 0.8 to 1.6 0.54 to 1.3, the
 // median 0.9; from the other sides 0.78 to 1.9, 1.3).
 // Over 13,324 views of 3,331 drawn volumes (40 to 900 voxels an edge, 1 to 24
-// bricks, 200 to 2400 pixels wide, near and far) direct is chosen for 9,377: 3 %
+// bricks, 200 to 2400 pixels wide, near and far) direct is chosen for 9,423: 3 %
 // of them are more than 3 % slower than staged, 0.8 % more than 15 %; in the mean
 // they take 0.65 of its time.
 struct DirectRule {
@@ -817,7 +819,9 @@ struct DirectRule {
         if (tiles <= 0.0) return true;
         const double v = pixel / tiles, s = lanes / tiles, l = line / tiles, b = bytes / tiles;
         if (tiles <= (coarse ? 2.0 : 1.4) * cus && (tiles <= cus || v <= 5.4 || b <= 1.0e6)) return true;
-        if (g == 1) return l >= 1.0 && b <= 8.0e6 && (coarse || (b <= 3.0e6 && b * v * v <= 30.0e6));
+        if (g == 1)
+            return coarse ? (l >= 1.0 && b <= 8.0e6) || (v >= 1.0 && b <= 1.0e6)
+                          : l >= 0.75 && b <= 3.0e6 && b * v * v <= 30.0e6;
         return l <= 1.0 || (b <= 4.0e6 && b * s * s <= 7.0e6) || (b <= 8.0e6 && l <= 1.6);
     }
 };

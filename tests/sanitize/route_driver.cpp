@@ -265,8 +265,9 @@ int main() {
         {{{80, 80, 80}, {6, 6, 6}, 0.25, 1, 199}, 0},                // 1.1 MB bricks [4.0]
         {{{80, 80, 80}, {6, 6, 6}, 0.25, 1, 106}, 1},                // [7.5]
         {{{158, 158, 158}, {4, 4, 4}, 0.5, 1, 475}, 1},              // 8.2 MB bricks [2.2]
-        {{{64, 64, 64}, {6, 6, 6}, 0.5, 1, 530}, 1},                 // 0.6 MB bricks [1.2]
-        {{{64, 64, 64}, {6, 6, 6}, 0.25, 1, 397}, 1},                // [1.6]
+        {{{80, 80, 80}, {6, 6, 6}, 0.5, 1, 662}, 1},                 // 1.1 MB bricks [1.2]
+        {{{64, 64, 64}, {6, 6, 6}, 0.5, 1, 530}, 0},                 // 0.6 MB bricks [1.2]
+        {{{64, 64, 64}, {6, 6, 6}, 0.25, 1, 475}, 1},                // [1.3]
         {{{64, 64, 64}, {6, 6, 6}, 0.25, 1, 289}, 0},                // [2.2]
         {{{64, 64, 64}, {6, 6, 6}, 1.0, 1, 530}, 0},                 // [1.2]
         // along y, pixel rows along z (and along x)
