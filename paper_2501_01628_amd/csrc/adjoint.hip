@@ -18,12 +18,16 @@
 // (a product over the ray gathers two roundings a sample).
 // One lane per ray, from transmittance checkpoints, left the GPU to its
 // longest rays: at 512x512 on 128^3 the slowest of 3,016 wavefronts ran 3.4
-// times the average, 2 to 3 per SIMD.  Bound by the vector ALU (60 % of its
-// issue slots, 70 % of the lanes active) and by the voxel atomics (13 % of the
-// time of 128^3 at 512x512, 36 % of 16 bricks of 512 x 256 x 256 at 384x384).
-// Forward and backward of 8 views of the former, step 0.5: 8.03 ms before,
-// 4.85 now; of one view of the latter, float16, step 0.25: 5.33 ms before, 3.91
-// now.  8 lanes a ray: 1 % and 12 % slower (set-up, partly filled stretches).
+// times the average, 2 to 3 per SIMD.  Bound by the vector ALU (76 % of its
+// issue slots while a CU is busy, 56 % of the lanes active; 16 bricks of 512 x
+// 256 x 256 at 384x384 65 % and 51 %) and by the voxel atomics (13 % of the time
+// of the former, 36 % of the latter).  Forward and backward of 8 views of the
+// former, step 0.5: 7.2 ms before, 4.4 now; of one view of the latter, float16,
+// step 0.25: 7.4 ms before, 6.4 now, of which 3.0 here.  8 lanes a ray: 1 % and
+// 12 % slower (set-up, partly filled stretches).  A view into a few voxels, bound
+// by the atomics alone, pays for the corners at the stretches' ends: 128 x 112 x
+// 96 in 6 bricks, a tenth of the field of view over 256x192, 2.5 ms before, 2.65
+// now; 80 x 60 x 90 in 8, half of it over 343x245, 1.31 and 1.37.
 // The opacity a_k = 1 - exp2(-a'_k) with a' the pre-scaled table opacity;
 // table gradients are summed per lane while consecutive samples use one
 // table segment, accumulated per workgroup in LDS (ds_add_f32) and flushed
