@@ -749,15 +749,17 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
 // * for float32 bricks seen at few voxels a pixel, where the lanes of a
 //   wavefront share the lines they read: up to sqrt(1.28 step) voxels a pixel
 //   with the step in voxels, since a coarse step has fewer samples per staged
-//   voxel, and up to 0.75 (20 MB / brick)^(1/4), since the lines of a large
-//   brick that the rays of a tile cross are in no cache any more (six views of
-//   seven volumes in 1, 8 and 24 bricks, the worst view and the best: bricks of
-//   6 and 11 MB at 0.8, step 0.5, 1.05 and 1.74, at 1.1, step 1, 0.97 and 1.5; of
-//   17 to 23 MB at 0.6 1.01 and 1.65, at 0.8 0.79 and 1.66, at 1.1 0.79 and 1.55;
-//   of 33 to 70 MB at 0.57, step 1, 0.98 and 1.9, at 0.8 0.75 and 1.5; of 125 to
-//   260 MB at 0.4 0.88 and 1.5, at 0.8 0.75 and 1.3; of 456 to 990 MB at 0.4 0.82
-//   and 1.5, at 0.8 0.68 and 1.5).  float16 bricks stage twice the voxels in the
-//   same LDS: direct is 0.64 to 1.04 times as fast there;
+//   voxel, and up to 1.5 (20 MB / brick)^(1/4), half that along y unless the
+//   pixel rows run along x: the lines of a large brick that the rays of a tile
+//   cross are in no cache any more (162 drawn views of bricks of 4 MB to 1 GB between
+//   the halved and the whole line: along x and z 0.75 to 1.6, the mean 1.10, at
+//   0.45 to 0.8 voxels a pixel; along y 0.7 to 1.3, 0.93.  Six views of seven volumes in 1, 8
+//   and 24 bricks, the worst view and the best: bricks of 6 and 11 MB at 0.8, step
+//   0.5, 1.05 and 1.74, at 1.1, step 1, 0.97 and 1.5; of 17 to 23 MB at 0.8 0.79
+//   and 1.66; of 33 to 70 MB at 0.8 0.75 and 1.5; of 125 to 260 MB at 0.8 0.75 and
+//   1.3; of 456 to 990 MB at 0.4 0.82 and 1.5, at 0.8 0.68 and 1.5).  float16 bricks
+//   stage twice the voxels in the same LDS: direct is 0.64 to 1.04 times as fast
+//   there;
 // * for small bricks, whose voxels stay in the caches.  float32: of up to 4 MB
 //   (an XCD's L2) while brick x (voxels a pixel)^2, the bytes that a pixel's
 //   surroundings span, is below 7 MB (216 to 512 bricks, steps 0.25 to 1: of 0.16
@@ -765,25 +767,26 @@ static int queue_workgroups(vr_context ctx, StorageK st, bool staged, int stagin
 //   3 1.0, at 5.5 0.74 to 1.1; of 1.2 MB at 2.2 1.13 to 1.2, at 3 0.89 to 1.03,
 //   at 4 0.70 to 0.8; of 2.2 MB at 1.6 1.07 to 1.17, at 2.2 0.91 to 1.02, at 4
 //   0.81 to 0.86), and of twice that up to 1.6 of the line above (4.2 MB at 1.2,
-//   step 0.5, 1.25; 8 MB at 1.0, step 0.5, 1.1).  float16: up to 8 MB from
-//   1 / sqrt(step) voxels a pixel on, where few samples share a staged voxel, and
-//   up to 1 MB from one on at half a voxel a step or more (a hundred volumes from
-//   all sides: step 0.5, 1 to 8 MB, at 1.0 to 1.2 0.80 to 1.3, the median 0.99, at
-//   1.5 to 3 1.0 to 2.2, 1.35; up to 1 MB at 1.0 to 1.2 0.88 to 1.5, 1.1, batches
-//   1.35 and 1.6; step 1 at 1.0 to 1.2 1.03 to 2, 1.3); at a step below half a
-//   voxel from 0.75 / sqrt(step) on (step 0.25 at 1.0 to 1.5 0.60 to 1.3, 0.93; at
-//   1.5 to 3 0.84 to 1.5, 1.1) up to 3 MB and 30 MB of brick x (voxels a pixel)^2
-//   (of 0.6 MB at 4 1.4, at 5.5 and 7.5 0.98; of 1.1 MB at 4 1.3, at 7.5 0.73; of
-//   2.1 MB at 3 1.12, at 4 0.90; of 4 MB at 1.2 to 1.6 0.85
-//   to 0.89).
+//   step 0.5, 1.25; 8 MB at 1.0, step 0.5, 1.1).  float16, where few samples
+//   share a staged voxel: from 1 / sqrt(step) voxels a pixel on for views along y,
+//   0.78 of that for the others (up to 8 MB, step 0.5: along y at 1.0 to 1.3 0.8 to
+//   1.2, the mean 0.95, along x and z at 1.1 to 1.4 0.9 to 1.4, 1.14; at 1.5 to 3
+//   1.0 to 2.2, 1.35; step 1 at 1.0 to 1.2 1.03 to 2, 1.3), at half a voxel a step
+//   or more not below one, and from one on up to 1 MB (at 1.0 to 1.2 0.88 to 1.5, 1.1,
+//   batches 1.35 and 1.6); at finer steps from 0.65 of it up to 1 MB, 0.75 up to 4
+//   and 0.9 up to 8 MB on (step 0.25: of 1 MB at 1.0 to 1.2 1.0, at 1.45 1.07; of 2
+//   to 4 MB at 1.0 to 1.3 0.87, at 1.3 to 2 1.02; of 4 to 8 MB at 1.0 to 1.5 0.85, at
+//   2 to 3 1.11), while brick x (voxels a pixel)^2 is below 30 MB, 60 for bricks
+//   above 3 MB (of 0.6 MB at 4 1.4, at 5.5 and 7.5 0.98; of 1.1 MB at 4 1.3, at 7.5
+//   0.73; of 2.1 MB at 3 1.12, at 4 0.90).
 // Views along y whose pixel rows run along z, where neighbouring lanes share no
 // line, count twice the voxels a pixel in the lines of float32 (bricks to 30 MB
 // at 0.4 of the line 1.1 to 1.9, at 0.6 0.7 to 1.3, at 0.8 to 1.6 0.54 to 1.3, the
 // median 0.9; from the other sides 0.78 to 1.9, 1.3).
 // Over 13,324 views of 3,331 drawn volumes (40 to 900 voxels an edge, 1 to 24
-// bricks, 200 to 2400 pixels wide, near and far) direct is chosen for 9,423: 3 %
-// of them are more than 3 % slower than staged, 0.8 % more than 15 %; in the mean
-// they take 0.65 of its time.
+// bricks, 200 to 2400 pixels wide, near and far) direct is chosen for 9,656: 3.6 %
+// of them are more than 3 % slower than staged, 1 % more than 15 %; in the mean
+// they take 0.66 of its time.
 struct DirectRule {
     int g, cus;
     // sums weighted by a job's tiles: voxels a pixel at the brick's centre, the
@@ -805,14 +808,18 @@ struct DirectRule {
         const double vpp = std::fabs(depth) * 2.0 * c.ay / ((double)c.height * fine);
         const double size = (g == 0 ? 4.0 : 2.0) * b.sdim[0] * b.sdim[1] * b.sdim[2];
         coarse = coarse || 2.0 * p.dt >= fine;
-        const bool along_y = std::fabs(c.f[1]) > std::max(std::fabs(c.f[0]), std::fabs(c.f[2])) &&
-                             std::fabs(c.r[1]) + std::fabs(c.r[2]) > 0.6 * (std::fabs(c.u[1]) + std::fabs(c.u[2]));
-        const double apart = g == 0 && along_y ? 2.0 * vpp : vpp;
+        // how far the pixel rows of a view along y run along z (0: along x)
+        const double turn = std::fabs(c.f[1]) > std::max(std::fabs(c.f[0]), std::fabs(c.f[2]))
+                                ? (std::fabs(c.r[1]) + std::fabs(c.r[2])) /
+                                      std::max(std::fabs(c.u[1]) + std::fabs(c.u[2]), 1e-9)
+                                : -1.0;
+        const double apart = g == 0 && turn > 0.8 ? 2.0 * vpp : vpp;
         tiles += t;
         pixel += t * vpp;
         lanes += t * apart;
-        line += t * apart / (g == 1 ? std::sqrt(fine / p.dt)
-                                    : std::min(std::sqrt(1.28 * p.dt / fine), 0.75 * std::pow(20.0e6 / size, 0.25)));
+        line += t * (g == 1 ? vpp * std::sqrt(p.dt / fine) * (turn >= 0.0 ? 0.78 : 1.0)
+                            : apart / std::min(std::sqrt(1.28 * p.dt / fine),
+                                               (turn > 0.3 ? 0.75 : 1.5) * std::pow(20.0e6 / size, 0.25)));
         bytes += t * size;
     }
     bool direct() const {
@@ -820,8 +827,9 @@ struct DirectRule {
         const double v = pixel / tiles, s = lanes / tiles, l = line / tiles, b = bytes / tiles;
         if (tiles <= (coarse ? 2.0 : 1.4) * cus && (tiles <= cus || v <= 5.4 || b <= 1.0e6)) return true;
         if (g == 1)
-            return coarse ? (l >= 1.0 && b <= 8.0e6) || (v >= 1.0 && b <= 1.0e6)
-                          : l >= 0.75 && b <= 3.0e6 && b * v * v <= 30.0e6;
+            return coarse ? v >= 1.0 && (b <= 1.0e6 || (l >= 0.78 && b <= 8.0e6))
+                          : l >= (b <= 1.0e6 ? 0.65 : b <= 4.0e6 ? 0.75 : 0.9) && b <= 8.0e6 &&
+                                b * v * v <= (b <= 3.0e6 ? 30.0e6 : 60.0e6);
         return l <= 1.0 || (b <= 4.0e6 && b * s * s <= 7.0e6) || (b <= 8.0e6 && l <= 1.6);
     }
 };
@@ -2197,7 +2205,8 @@ static bool tet_alone(int32_t n, const vr_tetpart* parts, const std::vector<int3
         const double surface = 2.0 * (a * b + b * c + c * a);
         if (surface > 0.0) chords += (prefix[i + 1] - prefix[i]) * (4.0 * a * b * c / surface / dt);
     }
-    return (tiles >= 28000.0 && tiles >= 400.0 * std::cbrt(tets)) || (tiles >= 10000.0 && chords <= 3.4 * tiles) || (tiles >= 6000.0 && chords <= 1.5 * tiles);
+    return (tiles >= 28000.0 && tiles >= 400.0 * std::cbrt(tets)) || (tiles >= 10000.0 && chords <= 3.4 * tiles) ||
+           (tiles >= 6000.0 && chords <= 1.5 * tiles);
 }
 
 // The frame of n parts, `stages` a mask of the kTet* stages (march into the

@@ -251,10 +251,12 @@ int main() {
         {{{100, 100, 100}, {5, 5, 5}, 0.5, 0, 690}, 0},              // 4.2 MB bricks [1.2]
         {{{100, 100, 100}, {5, 5, 5}, 0.5, 0, 376}, 1},              // [2.2]
         {{{192, 192, 128}, {2, 2, 2}, 0.5, 0, 1080}, 0},             // 19 MB bricks [0.59]
-        {{{256, 256, 256}, {2, 2, 2}, 0.5, 0, 1082}, 1},             // 69 MB bricks [0.78]
+        {{{256, 256, 256}, {2, 2, 2}, 0.5, 0, 1082}, 0},             // 69 MB bricks [0.78]
+        {{{256, 256, 256}, {2, 2, 2}, 0.5, 0, 1082, 30.0, 60.0}, 1},
         {{{256, 256, 256}, {2, 2, 2}, 0.5, 0, 2120}, 0},             // [0.4]
         {{{250, 900, 500}, {1, 1, 1}, 1.0, 0, 1345}, 1},             // 456 MB [1.11]
-        {{{250, 900, 500}, {1, 1, 1}, 0.5, 0, 2485}, 1},             // [0.6]
+        {{{250, 900, 500}, {1, 1, 1}, 0.5, 0, 2485}, 0},             // [0.6]
+        {{{250, 900, 500}, {1, 1, 1}, 0.5, 0, 2485, 30.0, 60.0}, 1},
         {{{2300, 1100, 40}, {1, 1, 1}, 1.0, 0, 3432}, 1},            // slices of 10 MB [1.11]
         {{{256, 512, 256}, {4, 2, 2}, 0.5, 0, 1080}, 1},             // 16 bricks of 1024 x 1024 x 512 at full HD
         {{{128, 128, 128}, {2, 2, 2}, 0.5, 0, 2000, 100.0, 20.0}, 0},
@@ -265,7 +267,9 @@ int main() {
         {{{80, 80, 80}, {6, 6, 6}, 0.25, 1, 199}, 0},                // 1.1 MB bricks [4.0]
         {{{80, 80, 80}, {6, 6, 6}, 0.25, 1, 106}, 1},                // [7.5]
         {{{158, 158, 158}, {4, 4, 4}, 0.5, 1, 475}, 1},              // 8.2 MB bricks [2.2]
-        {{{80, 80, 80}, {6, 6, 6}, 0.5, 1, 662}, 1},                 // 1.1 MB bricks [1.2]
+        {{{80, 80, 80}, {6, 6, 6}, 0.5, 1, 662}, 0},                 // 1.1 MB bricks [1.2]
+        {{{80, 80, 80}, {6, 6, 6}, 0.5, 1, 662, 30.0, 60.0}, 1},
+        {{{125, 125, 125}, {4, 4, 4}, 0.25, 1, 330}, 0},             // 4.1 MB bricks [2.5]
         {{{64, 64, 64}, {6, 6, 6}, 0.5, 1, 530}, 0},                 // 0.6 MB bricks [1.2]
         {{{64, 64, 64}, {6, 6, 6}, 0.25, 1, 475}, 1},                // [1.3]
         {{{64, 64, 64}, {6, 6, 6}, 0.25, 1, 289}, 0},                // [2.2]
